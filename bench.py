@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # plain copy of known size (2.0 and 1.0), keyed by the workload/settings and by
 # a hash of the kernel's sources: a changed kernel reports null.
 # the scaled solve's device code and the host code that sets its launch and stopping parameters
-SOLVE_SOURCES = ("pcg3.hip", "ssp_fused.h", "ssp_device.h", "ssp_host.h", "host.hip")
+SOLVE_SOURCES = ("pcg3.hip", "pcg4.hip", "ssp_scaled.h", "ssp_fused.h", "ssp_device.h", "ssp_host.h", "host.hip")
 MEASURED_TRAFFIC = {
     # (workload, pc, precision, kernel): (sources sha256[:16], HBM bytes of one solve): rocprofv3 FETCH_SIZE x 2.0
     # + WRITE_SIZE x 1.0 (KiB, the factors a plain 1 GiB copy reads), summed over the three k_pcg3 instances (nx 6,
@@ -58,7 +58,8 @@ def solve_sources_hash(sources=SOLVE_SOURCES) -> str:
     return h.hexdigest()[:16]
 
 
-def algorithmic_bytes(b, iters, outer, pc: str, precision: str, kernel: int = 0, onchip=None) -> np.ndarray:
+def algorithmic_bytes(b, iters, outer, pc: str, precision: str, kernel: int = 0, onchip=None,
+                      chip=None) -> np.ndarray:
     """Bytes the solve must stream per problem in the library's storage format:
     every stored block element each pass reads, once per pass, plus gamma in
     and lambda out once.  D_k and D_k^-1 are symmetric and stored packed
@@ -77,7 +78,7 @@ def algorithmic_bytes(b, iters, outer, pc: str, precision: str, kernel: int = 0,
     their sum.
     """
     if kernel == 4:
-        blk, vec = scaled_bytes(b, iters, outer, precision, onchip)
+        blk, vec = scaled_bytes(b, iters, outer, precision, onchip, chip)
         return blk + vec
     N = b.N.astype(np.float64)
     nx = b.nx.astype(np.float64)
@@ -109,7 +110,22 @@ def onchip_mask(b, pc: str, precision: str, mapping) -> np.ndarray:
     return np.array([int(b.N[i]) <= hor[int(b.nx[i])] for i in range(b.P)], dtype=bool)
 
 
-def scaled_bytes(b, iters, outer, precision: str, onchip=None):
+def chip_mask(b, precision: str, default_mapping: bool) -> np.ndarray:
+    """Problems the scaled solve holds on chip (the library's rule): FP32
+    storage, the default mapping, horizons whose vectors fit a CU's LDS, and
+    at nx 6 no more problems than the CUs take in a few rounds."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    limit = {6: 2128, 14: 768, 26: 360}
+    ok = np.array([precision != "fp64" and default_mapping and int(b.N[i]) <= limit.get(int(b.nx[i]), 0)
+                   for i in range(b.P)], dtype=bool)
+    small = ok & (b.nx == 6)
+    if small.any() and small.sum() > (2.5 if b.N[small].max() <= 256 else 1.0) * cus:
+        ok &= ~small
+    return ok
+
+
+def scaled_bytes(b, iters, outer, precision: str, onchip=None, chip=None):
     """Bytes the scaled solve must move per problem, split into block bytes
     and vector bytes.  Per PCG pass (iters + outer passes: one initial pass
     per inner solve) it streams Oh_k (N - 1 blocks of nx^2 in the storage
@@ -133,6 +149,9 @@ def scaled_bytes(b, iters, outer, precision: str, onchip=None):
     st = outer.astype(np.float64)
     rows = N * nx
     passes = it + st
+    if chip is not None:
+        passes = np.where(chip, st, passes)
+        onchip = chip if onchip is None else onchip | chip
     sweeps = np.maximum(st - 1, 0)  # zero start: the first outer step takes gamma as its residual
     blk = e * (N - 1) * nn * passes + 2 * e * N * nn * st + 8.0 * (N * npk + (N - 1) * nn) * sweeps
     ve = np.where(onchip, 0.0, e) if onchip is not None else e  # storage-type vector bytes per element in HBM
@@ -318,9 +337,10 @@ def main() -> int:
         db.solver.set_mapping(args.threads or 128, args.lds, args.kernel)
     stream = torch.cuda.current_stream()
     mapping = None
+    db.build(args.pc, precision)
+    default_mapping = db.solver.scaled_mapping()[:2]
     if args.mapping:
         # a fixed per-state-size mapping, "nx:threads:lds,..." (e.g. from an earlier autotune)
-        db.build(args.pc, precision)
         for item in args.mapping.split(","):
             if item.startswith("scaled:"):
                 t_, l_ = (int(v) for v in item.split(":")[1:])
@@ -330,7 +350,6 @@ def main() -> int:
             db.solver.set_group_mapping(nx_, t_, l_)
         mapping = db.solver.mapping()
     elif args.autotune and not (args.threads or args.lds or args.kernel):
-        db.build(args.pc, precision)
         mapping = db.autotune(tol)
         print(f"[bench] autotuned mapping (nx, threads, lds, ms): {mapping}", file=sys.stderr, flush=True)
     else:
@@ -420,13 +439,16 @@ def main() -> int:
     if args.graph:
         ok = ok and all(r["graph_matches_eager"] for r in runs.values())
     kern, coop_w, coop_g = db.solver.solve_kernel()  # the kernel the solves ran: 1 explicit, 2 fused, 3 cooperative
-    oc = onchip_mask(b, args.pc, precision, db.solver.scaled_mapping()) if kern == 4 else None
-    bytes_solve = float(algorithmic_bytes(b, res["iters"], res["outer"], args.pc, precision, kern, oc).sum())
+    sm = db.solver.scaled_mapping()
+    is_default = sm[:2] == default_mapping
+    oc = onchip_mask(b, args.pc, precision, sm) if kern == 4 else None
+    ch = chip_mask(b, precision, is_default) if kern == 4 else None
+    bytes_solve = float(algorithmic_bytes(b, res["iters"], res["outer"], args.pc, precision, kern, oc, ch).sum())
     split = None
     if kern == 4:
-        bb, vb = scaled_bytes(b, res["iters"], res["outer"], precision, oc)
+        bb, vb = scaled_bytes(b, res["iters"], res["outer"], precision, oc, ch)
         split = {"block_bytes": float(bb.sum()), "vector_bytes": float(vb.sum()),
-                 "problems_with_vectors_in_lds": int(oc.sum())}
+                 "problems_with_vectors_in_lds": int((oc | ch).sum()), "problems_on_chip": int(ch.sum())}
     rec = MEASURED_TRAFFIC.get((args.workload, args.pc, precision, args.kernel))
     traffic = rec[1] if rec and rec[0] == solve_sources_hash() else None
     solve_avg_s = float(plain["solve_ms"].mean()) / 1e3
@@ -455,7 +477,8 @@ def main() -> int:
             r = db.results()
             pk = db.solver.solve_kernel()[0]
             oc = onchip_mask(b, pc, precision, db.solver.scaled_mapping()) if pk == 4 else None
-            by = float(algorithmic_bytes(b, r["iters"], r["outer"], pc, precision, pk, oc).sum())
+            ch = chip_mask(b, precision, is_default) if pk == 4 else None
+            by = float(algorithmic_bytes(b, r["iters"], r["outer"], pc, precision, pk, oc, ch).sum())
             compare[pc] = {"iters_mean": round(float(r["iters"].mean()), 3),
                            "outer_mean": round(float(r["outer"].mean()), 3),
                            "max_relres": float(r["relres"].max()),
@@ -567,7 +590,7 @@ def main() -> int:
             "kkt": kkt,
         },
         "roofline": {
-            "kernel": {1: "k_pcg", 2: "k_pcg2", 3: "k_coop", 4: "k_pcg3"}[kern],
+            "kernel": {1: "k_pcg", 2: "k_pcg2", 3: "k_coop", 4: "k_pcg4 and k_pcg3" if kern == 4 and ch.any() else "k_pcg3"}[kern],
             "bound": "hbm",
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,
@@ -577,7 +600,8 @@ def main() -> int:
             **({"note": "latency-bound: blocks stay in LDS, one grid-wide sum per PCG iteration"}
                if kern == 3 else
                {"note": "one persistent instance per state size, run concurrently; achieved and traffic cover "
-                        "all of them over the solve phase"} if kern == 4 else {}),
+                        "all of them over the solve phase; problems held on chip count their blocks once per inner "
+                        "solve, their passes are bound by LDS and latency"} if kern == 4 else {}),
         },
         "cpu_baseline": cpu,
     }

@@ -311,7 +311,10 @@ __global__ void k_export(BuildArgs a, int which, const TM *hi, const float *lo, 
         } else if (which == 2) {
             v = (double)hi[kb + bp + bs + packed_index(r, c, nx)];
         } else {
-            v = (double)hi[a.off_blk[p] + (int64_t)k * bs + e];
+            const int el = which == 4 && lane_major<TM, kLaneMajorNx>() && nx == kLaneMajorNx
+                               ? lane_major_place<kLaneMajorNx>(r, c)
+                               : e;
+            v = (double)hi[a.off_blk[p] + (int64_t)k * bs + el];
         }
         dst[o + e] = v;
     }

@@ -514,7 +514,15 @@ __global__ __launch_bounds__(kThreads) void k_build_ohat_nx(BuildArgs a, const i
         wave_sync();
         wave_sync();
     }
-    if (ln.row) store_split_row<TM, NX>((TM *)a.OH + ol + i * NX, (float *)nullptr, t, 1.0);
+    if constexpr (lane_major<TM, NX>()) {
+        if (ln.row)
+            static_for<0, NX / 2>([&](auto hc) {
+                constexpr int j = 2 * decltype(hc)::value;
+                *(f32x2 *)((TM *)a.OH + ol + lane_major_place<NX>(i, j)) = f32x2{(float)t[j], (float)t[j + 1]};
+            });
+    } else {
+        if (ln.row) store_split_row<TM, NX>((TM *)a.OH + ol + i * NX, (float *)nullptr, t, 1.0);
+    }
 }
 
 template <int NX>

@@ -743,7 +743,22 @@ __global__ __launch_bounds__(kThreadsD) void k_bdpp_ohat(BuildArgs a, const int2
         });
     });
     keep(o);
-    store_split_slots<TM, NX>((TM *)a.OH + oblk + (int64_t)kc * bs, (float *)nullptr, d, o, 1.0);
+    TM *out = (TM *)a.OH + oblk + (int64_t)kc * bs;
+    if constexpr (lane_major<TM, NX>()) {  // this lane's rows are its vectors of the block
+        static_assert(P == NX / 2 && R == 2, "lane-major order");
+        if (d.act && d.p < P)
+            static_for<0, NX / 2>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                f32x4 v;
+                static_for<0, 4>([&](auto ec) {
+                    constexpr int e = decltype(ec)::value, f = 4 * t + e;
+                    v[e] = (float)o[f / NX][f % NX];
+                });
+                *(f32x4 *)(out + 4 * (t * P + d.p)) = v;
+            });
+    } else {
+        store_split_slots<TM, NX>(out, (float *)nullptr, d, o, 1.0);
+    }
 }
 
 template <int NX>

@@ -79,15 +79,18 @@ bool scaled_possible(const ssp_batch *b) {
 // LDS budget of the scaled kernel: the largest step of every state size in
 // the batch (or the tuned / set budget), at least what the FP64 residual's
 // staged fallback needs.
-int scaled_lds(const ssp_batch *b, int threads, int m) {
+int scaled_lds(const ssp_batch *b, int threads, int m, int set) {
     int need = 0;
     for (const auto &g : b->groups) need = std::max(need, ssp::pcg3_lds(g.nx, b->fp32, threads, m));
-    int l = b->s3_lds > 0 ? b->s3_lds : need;
+    int l = set > 0 ? set : need;
     // the FP64 residual needs one knot per step of every state size
     for (const auto &g : b->groups)
         while (l < ssp::kFusedLdsCap && ssp::pcg3_residual_steps(g.nx, b->fp32, l) < 1) l += 256;
     return std::min(l, ssp::kFusedLdsCap);
 }
+
+int scaled_lds(const ssp_batch *b, int threads, int m) { return scaled_lds(b, threads, m, b->s3_lds); }
+int scaled_lds_default(const ssp_batch *b, int threads, int m) { return scaled_lds(b, threads, m, 0); }
 
 // the scaled kernel can run every state size of the batch with this budget
 bool scaled_fits(const ssp_batch *b, int threads, int lds, int m) {
@@ -291,12 +294,16 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
     // preconditioned S, so the first inner solve may aim at theta tol itself
     // (no floor above it): one outer step then suffices for most problems
     a.tau_min = b->prec == SSP_FP64 ? 1e-15 : std::min(1e-6, a.theta * a.tol);
+    // The problems that fit a CU's registers and LDS run the on-chip solve when the mapping is the default one (it
+    // repeats that mapping's sums, and returns the same bits); the longer ones, which come first in their group's
+    // order, and any other mapping stream.
+    const bool chip = b->fp32 && !a.acc64 && t == 256 && a.lds_bytes == scaled_lds_default(b, t, a.poly);
     // one persistent grid per state size (largest total work first), each
     // with its own queue counter, on internal streams forked from and joined
     // back into s: a grid whose queue is empty retires and the next size's
     // workgroups take its place
     const int ng = (int)b->groups.size();
-    SSP_HIP(ssp::launch_fill_i32((int32_t *)a.queue, 0, ng, s));
+    SSP_HIP(ssp::launch_fill_i32((int32_t *)a.queue, 0, 2 * ng, s));
     const bool fork = ng > 1;
     if (fork) {
         SSP_HIP(hipEventRecord(b->gevents[ng], s));
@@ -306,9 +313,17 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
         const auto &g = b->groups[i];
         ssp::SolveArgs ga = a;
         ga.order = b->dgorder + g.offset;
-        ga.nprob = g.count;
-        ga.queue = a.queue + i;
+        ga.queue = a.queue + 2 * i;
+        ga.step_knots = ssp::pcg3_steps_for(g.nx, b->fp32, t, a.lds_bytes, a.poly);
+        ga.res_knots = ssp::pcg3_residual_steps(g.nx, b->fp32, a.lds_bytes);
+        const int streamed = chip && ga.step_knots > a.poly + 1 ? g.streamed : g.count;
+        ga.nprob = streamed;
         SSP_HIP(ssp::launch_pcg3(ga, b->fp32, t, g.nx, 0, fork ? b->gstreams[i] : s));
+        ga.order += streamed;
+        ga.queue += 1;
+        ga.nprob = g.count - streamed;
+        ga.lds_bytes = g.chip_lds;
+        SSP_HIP(ssp::launch_pcg4(ga, g.nx, fork ? b->gstreams[i] : s));
     }
     if (fork) {
         for (int i = 0; i < ng; ++i) {
@@ -424,7 +439,7 @@ ssp_status autotune_scaled(ssp_batch *b, double rel_tol, const double *gamma, do
     }
     if (best_t) {
         b->s3_threads = best_t;
-        b->s3_lds = best_l;
+        b->s3_lds = best_l == scaled_lds_default(b, best_t, m) ? 0 : best_l;
         b->s3_tuned_ms = best;
     } else {
         b->s3_threads = 256;
@@ -536,12 +551,32 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
         std::stable_sort(b->groups.begin(), b->groups.end(),
                          [](const ssp_batch::Group &u, const ssp_batch::Group &v) { return u.work > v.work; });
     }
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
     std::vector<int32_t> gorder;
     for (auto &g : b->groups) {
         g.offset = (int)gorder.size();
         for (int32_t p : order)
             if (nx[p] == g.nx) gorder.push_back(p);
         g.count = (int)gorder.size() - g.offset;
+        // the on-chip solve's share: all six vectors in LDS for the longest of its problems where they fit
+        auto fits = [&](int32_t p) {
+            const int64_t l = ssp::pcg4_lds(g.nx, N[p], false);
+            return l >= 0 && l <= ssp::kLds4Cap;
+        };
+        while (g.streamed < g.count && !fits(gorder[g.offset + g.streamed])) ++g.streamed;
+        // At nx 6 a pass is all barriers and latency: three streaming workgroups per CU hide it better than one
+        // on-chip workgroup once there are problems enough (N 32 to 256, on-chip against streaming: 256 problems
+        // 0.224 and 0.367 ms, 512: 0.320 and 0.386, 768: 0.440 and 0.413, 1365: 0.781 and 0.513).
+        // With horizons beyond 256, whose later sets are read again at every product, the line is one problem per CU
+        // (N 480 to 500, 300 problems: 0.865 and 0.809 ms; N 980 to 1000, 64: 0.966 and 1.343, 512: 2.245 and 1.599).
+        if (g.nx == 6 && g.streamed < g.count) {
+            const int longest = N[gorder[g.offset + g.streamed]];
+            if (2 * (g.count - g.streamed) > (longest <= 256 ? 5 : 2) * cus) g.streamed = g.count;
+        }
+        if (g.streamed < g.count)
+            g.chip_lds = (int)std::min<int64_t>(ssp::pcg4_lds(g.nx, N[gorder[g.offset + g.streamed]], true),
+                                                ssp::kLds4Cap);
     }
     std::vector<int32_t> knot_prob((size_t)b->knots);
     for (int p = 0; p < nprob; ++p)
@@ -656,7 +691,7 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
         const size_t nn = b->off_nn[nprob], uu = b->off_uu[nprob], nv = b->off_v[nprob];
         if (dalloc(&b->Qinv, nn) != hipSuccess || dalloc(&b->Rinv, uu) != hipSuccess ||
             dalloc(&b->r64, nv) != hipSuccess || dalloc(&b->douter, (size_t)nprob) != hipSuccess ||
-            dalloc(&b->dqueue, std::max<size_t>(b->groups.size(), 1)) != hipSuccess)
+            dalloc(&b->dqueue, std::max<size_t>(2 * b->groups.size(), 1)) != hipSuccess)
             rc = SSP_ERR_ALLOC;
     }
     if (rc != SSP_OK) {
@@ -934,7 +969,7 @@ ssp_status ssp_export(ssp_batch *b, int which, double *diag, double *off, void *
         hipStream_t s = (hipStream_t)stream;
         ssp::BuildArgs a = build_args(b);
         SSP_HIP(ssp::launch_export(a, 3, b->Zs, nullptr, b->fp32, diag, b->knots, s));
-        SSP_HIP(ssp::launch_export(a, 3, b->OH, nullptr, b->fp32, off, b->knots, s));
+        SSP_HIP(ssp::launch_export(a, 4, b->OH, nullptr, b->fp32, off, b->knots, s));
         return SSP_OK;
     }
     if (!b->built) return SSP_ERR_STATE;

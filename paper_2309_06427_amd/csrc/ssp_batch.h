@@ -130,6 +130,8 @@ struct ssp_batch {
     struct Group {
         int nx = 0, count = 0, offset = 0;  // problems dgorder[offset .. offset + count)
         double work = 0;                    // sum of N nx^2 (launch order: largest first)
+        int streamed = 0, chip_lds = 0;     // scaled solve under FP32 storage: the first `streamed` problems are too
+                                            // long for the on-chip solve; LDS bytes of the others
         int threads = 0, lds = 0;
         float tuned_ms = 0.0f;  // best solve time the autotuner measured (0: not tuned)
     };

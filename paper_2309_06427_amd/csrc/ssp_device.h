@@ -10,6 +10,12 @@ namespace ssp {
 
 constexpr int kWave = 64;
 
+// Native clang vector types (LLVM first-class vectors, unlike HIP's struct
+// float4) so that arrays of them are split into registers.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
 // Per-problem status codes (numerically equal to the public SSP_P_* values).
 constexpr int kOk = 0, kNotSpd = 1, kMaxIter = 2, kNonFinite = 3, kBreakdown = 4;
 // one inner solve without refinement met the tolerance on its recurrence
@@ -40,10 +46,51 @@ __device__ __forceinline__ double uniform(double v) {
 
 // Butterfly sum over the 64 lanes of a wavefront.  Every lane ends with the
 // same bits: each stage adds the same two operands on both partner lanes.
+// All stages are register moves between lanes (half and quarter swaps, then
+// rotations of the 16-lane rows: after the stages before it the value has
+// period 2 o in a row, so lane i + o holds what lane i ^ o holds).  Through
+// the LDS permute each stage costs an LDS round trip of over 100 cycles.
+__device__ __forceinline__ void lane_swap32(int v, int &a, int &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void lane_swap16(int v, int &a, int &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+template <int O>
+__device__ __forceinline__ int row_rotate(int v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x120 + O, 0xf, 0xf, false);
+}
+template <int O>
+__device__ __forceinline__ float row_rotate(float v) { return __int_as_float(row_rotate<O>(__float_as_int(v))); }
+template <int O>
+__device__ __forceinline__ double row_rotate(double v) {
+    return __hiloint2double(row_rotate<O>(__double2hiint(v)), row_rotate<O>(__double2loint(v)));
+}
+template <bool HALF>
+__device__ __forceinline__ float swap_sum(float v) {
+    int a, b;
+    HALF ? lane_swap32(__float_as_int(v), a, b) : lane_swap16(__float_as_int(v), a, b);
+    return __int_as_float(a) + __int_as_float(b);
+}
+template <bool HALF>
+__device__ __forceinline__ double swap_sum(double v) {
+    int al, bl, ah, bh;
+    HALF ? lane_swap32(__double2loint(v), al, bl) : lane_swap16(__double2loint(v), al, bl);
+    HALF ? lane_swap32(__double2hiint(v), ah, bh) : lane_swap16(__double2hiint(v), ah, bh);
+    return __hiloint2double(ah, al) + __hiloint2double(bh, bl);
+}
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    v = swap_sum<true>(v);
+    v = swap_sum<false>(v);
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    v += row_rotate<1>(v);
     return v;
 }
 

@@ -14,12 +14,6 @@ namespace ssp {
 
 namespace {
 
-// Native clang vector types (LLVM first-class vectors, unlike HIP's struct
-// float4) so that arrays of them are split into registers.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-
 template <typename TM>
 struct Vec16;
 template <>

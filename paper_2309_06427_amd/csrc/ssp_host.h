@@ -72,6 +72,8 @@ struct SolveArgs {
     int poly;            // Horner steps m of the preconditioner polynomial in Oh (0: block-Jacobi)
     double pc_c;         // coefficient of each Horner step (1; 1/2 for the additive stair)
     int acc64;           // scaled solve: sum the FP32 inner products in FP64
+    int step_knots, res_knots;  // on-chip solve: knots per step of the streaming solve whose sums it repeats (of its
+                                // passes and its FP64 residual)
 };
 
 // Generic assembly (any nx <= 64), one 64-lane workgroup per knot of
@@ -109,7 +111,7 @@ hipError_t launch_build_blocks(const BuildArgs &a, const double *D, const double
 hipError_t launch_build_phi(const BuildArgs &a, int64_t knots, int nx_max, bool fp32, hipStream_t s);
 // Copy one stored block kind to the caller's FP64 layout (full nx x nx
 // blocks at off_nn): which = 0 D_k (+ packed remainder lo), 1 L_k (+ lo),
-// 2 D_k^-1, 3 the explicit stair blocks (array `hi`, stride bs).
+// 2 D_k^-1, 3 the explicit stair blocks or W_k (array `hi`, stride bs), 4 Oh_k (its stored order, stride bs).
 hipError_t launch_export(const BuildArgs &a, int which, const void *hi, const float *lo, bool fp32, double *dst,
                          int64_t knots, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *dst, int32_t v, int64_t n, hipStream_t s);
@@ -179,6 +181,12 @@ bool pcg2_threads_ok(int threads);
 // nx, problems taken from the device queue counter a.queue.  `grid`:
 // workgroups to launch (<= 0: as many as fit on the device at once).
 hipError_t launch_pcg3(const SolveArgs &a, bool fp32, int threads, int nx, int grid, hipStream_t s);
+// The same solve with the blocks and vectors of a problem on chip (FP32 storage, state sizes 6, 14, 26, FP32 sums):
+// one workgroup per CU, problems from a.queue.  The problem of N knots needs pcg4_lds(nx, N, false) bytes of LDS
+// (with all six vectors there pcg4_lds(nx, N, true); -1: no such state size), at most kLds4Cap.
+constexpr int kLds4Cap = 160 * 1024 - 256;
+int64_t pcg4_lds(int nx, int N, bool all_vectors);
+hipError_t launch_pcg4(const SolveArgs &a, int nx, hipStream_t s);
 // LDS bytes for the largest pipeline step of state size nx at `threads`
 // with m Horner steps (0 if it cannot run), and the knots per step a budget
 // gives (< 1: cannot run).

@@ -29,6 +29,27 @@ __host__ __device__ inline int knot_stride(int nx, int elem_bytes) {
     return 2 * packed_stride(nx, elem_bytes) + block_stride(nx, elem_bytes);
 }
 
+// Stored order of Oh under FP32 storage at state size 26 (the other blocks are row-major): the on-chip solve gives
+// lane p of a 16-lane group rows p and p + 13, 52 floats; the block is 13 x 13 vectors of 16 bytes, vector
+// 13 t + p holding entries 4 t .. 4 t + 3 of lane p's row pair, so that a vector load of a lane group reads 208
+// contiguous bytes.  (The row-major order costs such a load one cache line per lane.)
+constexpr int kLaneMajorNx = 26;
+template <typename TM, int NX>
+constexpr bool lane_major() { return sizeof(TM) == 4 && NX == kLaneMajorNx; }
+// row-major position of the entry stored at e, and back
+template <int NX>
+__host__ __device__ constexpr int lane_major_source(int e) {
+    constexpr int P = NX / 2;
+    const int v = e >> 2, t = v / P, p = v - t * P, f = 4 * t + (e & 3);  // entry f of row pair p
+    return f < NX ? p * NX + f : (p + P) * NX + f - NX;
+}
+template <int NX>
+__host__ __device__ constexpr int lane_major_place(int row, int col) {
+    constexpr int P = NX / 2;
+    const int p = row < P ? row : row - P, f = row < P ? col : col + NX;
+    return ((f >> 2) * P + p) * 4 + (f & 3);
+}
+
 // Staging geometry of one sweep.  Rows of a staged block are padded to
 // nx + 1 elements (odd for even nx) so that row-wise LDS reads by
 // consecutive lanes fall in distinct banks.
