@@ -274,7 +274,8 @@ ssp_status ssp_export(ssp_batch *b, int which, double *diag, double *off, void *
  *       block-Jacobi and both stairs under FP32 storage (except a single
  *       problem of N >= 24 knots, which runs the cooperative solve).
  * The choice takes effect at the next build.
- * The fused kernel is built for 128 and 256 threads and for knots that fit
+ * The fused kernel is built for 128 and 256 threads (FP64 storage also for
+ * 512, its default until a mapping is set) and for knots that fit
  * its LDS rings; otherwise the explicit kernel runs.  Returns SSP_ERR_ARG for
  * an unknown value or a budget that cannot hold one knot of the largest nx. */
 ssp_status ssp_set_mapping(ssp_batch *b, int32_t threads, int32_t lds_bytes, int32_t kernel);
@@ -344,7 +345,7 @@ ssp_status ssp_gemm_f32(int32_t M, int32_t N, int32_t K, const float *A, int32_t
  * in groups of one state size, each group launched on its own stream with its
  * own workgroup size and LDS budget (the budget sets the knots per pipeline
  * step, hence workgroups per CU).  ssp_autotune times every candidate
- * mapping (128 or 256 threads; the largest step and two shorter ones) on
+ * mapping (the FP64 default; 128 or 256 threads; the largest step and two shorter ones) on
  * each group alone with this batch's last build and keeps the fastest; it
  * then solves the whole batch once, so the outputs (same meaning as in
  * ssp_solve, zero start, max_iter = 10 N nx) hold valid results.  It

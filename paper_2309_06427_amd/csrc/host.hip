@@ -132,11 +132,20 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
 
 // Workgroup size and LDS bytes of the fused kernel for one solve group, or
 // lds = 0 if its knots do not fit the fused kernel's registers or LDS.
+//
+// FP64 without a chosen mapping: one workgroup of 512 threads per CU, whose step holds 6 to 80 knots of a problem,
+// where 128 threads hold one knot of 26 states, half a wave's work between two barriers.  Only where a small state
+// size leaves several small workgroups per CU with problems of their own are 256 threads better.  Measured, 128 /
+// 256 / 512 threads in ms: nx 26 x 1024 problems (106 iterations) 113 / 61 / 37, x 16 13.6 / 7.1 / 2.4; nx 20 x 512
+// 15.8 / 8.4 / 4.0; nx 14 x 1024 3.55 / 2.84 / 3.32, x 16 2.36 / 1.37 / 0.80; nx 9 x 512 1.81 / 1.02 / 1.02; nx 6 x
+// 1024 0.85 / 0.80 / 1.04, x 16 0.62 / 0.42 / 0.29.
 void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, int *lds) {
-    const int t = g.threads > 0 ? g.threads : b->threads;
+    const bool chosen = g.threads > 0 || b->mapping_set;
+    int t = g.threads > 0 ? g.threads : b->threads;
+    if (!chosen && !b->fp32) t = g.nx < 16 && g.count > 2 * b->cus ? 256 : 512;
     *threads = t;
     *lds = 0;
-    if (!ssp::pcg2_threads_ok(t)) return;
+    if (!ssp::pcg2_threads_ok(t) && (chosen || t != 512)) return;
     const int need = ssp::pcg2_lds(g.nx, b->fp32, t);
     if (need == 0) return;
     int l = g.lds > 0 ? g.lds : (b->lds_bytes > 0 ? b->lds_bytes : need);
@@ -551,8 +560,8 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
         std::stable_sort(b->groups.begin(), b->groups.end(),
                          [](const ssp_batch::Group &u, const ssp_batch::Group &v) { return u.work > v.work; });
     }
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 0;
+    if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) b->cus = 256;
+    const int cus = b->cus;
     std::vector<int32_t> gorder;
     for (auto &g : b->groups) {
         g.offset = (int)gorder.size();
@@ -750,6 +759,7 @@ ssp_status ssp_set_mapping(ssp_batch *b, int32_t threads, int32_t lds_bytes, int
     if (kernel < 0 || kernel > 4) return SSP_ERR_ARG;
     if (lds_bytes > 0 && lds_bytes < ssp::pcg_min_lds(b->nx_max, true)) return SSP_ERR_ARG;
     b->threads = threads;
+    b->mapping_set = true;
     b->lds_bytes = lds_bytes;
     b->kernel = kernel;
     for (auto &g : b->groups) g.threads = g.lds = 0;
@@ -1023,8 +1033,9 @@ ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, doubl
         auto &g = b->groups[gi];
         int best_t = 0, best_l = 0;
         float best = 0.0f;
-        for (int t : {128, 256}) {
-            for (int l : lds_candidates(b, g.nx, t)) {
+        for (int t : {0, 128, 256}) {  // 0: the default mapping
+            if (t == 0 && (b->fp32 || b->mapping_set)) continue;  // there one of the candidates below
+            for (int l : t ? lds_candidates(b, g.nx, t) : std::vector<int>{0}) {
                 g.threads = t;
                 g.lds = l;
                 float ms = 0.0f;
@@ -1040,7 +1051,7 @@ ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, doubl
                         fail(e, "autotune timing");
                 }
                 if (rc != SSP_OK) break;
-                if (best_t == 0 || ms < best) {
+                if (best == 0.0f || ms < best) {
                     best = ms;
                     best_t = t;
                     best_l = l;

@@ -40,9 +40,9 @@ namespace ssp {
 namespace {
 
 // 16-byte prefetch registers per thread (fewer for FP64, whose arithmetic
-// needs twice the registers)
+// needs twice the registers, in the small workgroups that share a CU)
 template <typename TM>
-constexpr int prefetch_slots() { return sizeof(TM) == 4 ? 12 : 8; }
+__host__ __device__ constexpr int prefetch_slots(int block) { return sizeof(TM) == 4 ? 12 : block == 512 ? 16 : 8; }
 
 // The six recurrence vectors of a problem.
 template <typename TI>
@@ -70,7 +70,7 @@ __host__ __device__ inline int pcg2_knots_per_step(int nx, int block, int lds_by
     const int ks = knot_stride(nx, sizeof(TM));
     const int nxp = (nx + V - 1) / V * V;
     int C = (block / 64) * (64 / nx);
-    const int Cp = (prefetch_slots<TM>() * block * V) / ks;
+    const int Cp = (prefetch_slots<TM>(block) * block * V) / ks;
     if (Cp < C) C = Cp;
     const int per = (ks + 4 * nxp) * (int)sizeof(TM);
     const int Cl = (lds_bytes - nxp * (int)sizeof(TM) - 16) / per - 2;  // + one u slot + 16-byte spot
@@ -87,7 +87,7 @@ template <typename TM, int BLOCK>
 struct Prefetch {
     using VT = typename Vec16<TM>::T;
     static constexpr int V = Vec16<TM>::V;
-    static constexpr int kPF = prefetch_slots<TM>();
+    static constexpr int kPF = prefetch_slots<TM>(BLOCK);
     VT reg[kPF];
     TM vec[6];       // u, w, p, s, x, r of this thread's lead row
     double res = 0;  // init pass: the FP64 residual of that row instead
@@ -646,6 +646,7 @@ hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, in
         switch (threads) {
             case 128: return launch2_nx<double, 128>(a, nprob, nx, s);
             case 256: return launch2_nx<double, 256>(a, nprob, nx, s);
+            case 512: return launch2_nx<double, 512>(a, nprob, nx, s);
         }
     }
     return hipErrorInvalidValue;

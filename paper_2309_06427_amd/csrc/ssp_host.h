@@ -173,7 +173,7 @@ hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, in
 int pcg2_lds(int nx_max, bool fp32, int threads);  // 0 if the mapping cannot hold one knot
 // Knots per step the fused kernel uses for state size nx (< 1: cannot run).
 int pcg2_steps_for(int nx, bool fp32, int threads, int lds_bytes);
-// Workgroup sizes the fused kernel is compiled for (128, 256).
+// Workgroup sizes a mapping may name (128, 256); the FP64 kernel is also compiled for 512, its default.
 bool pcg2_threads_ok(int threads);
 
 // Scaled solve of the problems order[0 .. nprob) (all of state size nx, one
