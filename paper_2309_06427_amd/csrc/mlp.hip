@@ -4,9 +4,8 @@
 // (forward, residual loss, backward, Adam) run in these kernels.
 //
 // Every product is an FP32 GEMM on the matrix cores
-// (v_mfma_f32_16x16x4_f32): 64 x 64 output tiles per 256-thread workgroup,
-// each wave a 32 x 32 quarter as 2 x 2 MFMA tiles, K staged through LDS 16 at
-// a time.  Operand loaders read the network inputs straight from the stored
+// (v_mfma_f32_16x16x4_f32): 32 x 32 output tiles per 256-thread workgroup,
+// each wave one MFMA tile, K staged through two LDS buffers 32 at a time.  Operand loaders read the network inputs straight from the stored
 // blocks (no feature matrix is materialised) and the epilogues fuse bias,
 // GELU and its derivative.  Weight gradients reduce over the knots with a
 // fixed K split and a fixed-order sum, so training steps are reproducible.
@@ -22,7 +21,8 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 64, BN = 64, BK = 16, GT = 256, PADL = 4;
+constexpr int T = 32, BK = 32, GT = 256, PADL = 4;
+constexpr int kSplitStep = 16;  // K ranges are multiples of this
 
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 
@@ -139,85 +139,105 @@ struct EpGeluBack {  // dZ = v * gelu'(Z)
 };
 
 // ------------------------------------------------------------------- GEMM ---
-// C = op(A) op(B) over k in [z * kspl, min(K, (z + 1) * kspl)), z = blockIdx.z.
+// C = op(A) op(B) over k in [z * kspl, min(K, (z + 1) * kspl)), z = blockIdx.z,
+// for a T x T tile of C per workgroup, each wave a 16 x 16 quarter of it.
+// Bound by the latency of its loads (short K ranges, operands gathered an
+// element at a time): 32 x 32 tiles, 8 workgroups per CU, beat 64 x 64 ones at
+// every size from 2304 to 57600 knots (a step's loss and gradient, nx 14, 2304
+// knots: 180 us with 64 x 64 tiles, 131 us; nx 26, 57600 knots: 3.95 and 3.66
+// ms).
 template <class AL, class BL, class EP>
 __global__ __launch_bounds__(GT) void k_gemm(int M, int N, int K, int kspl, AL al, BL bl, EP ep) {
-    __shared__ float As[BK][BM + PADL];
-    __shared__ float Bs[BK][BN + PADL];
+    __shared__ float As[2][BK][T + PADL];
+    __shared__ float Bs[2][BK][T + PADL];
+    constexpr int EA = T * BK / GT, EB = EA;  // elements per thread and operand
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, z = blockIdx.z;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+    const int m0 = blockIdx.x * T, n0 = blockIdx.y * T, z = blockIdx.z;
+    const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (T / 2);
     const int kb = z * kspl, ke = min(K, kb + kspl);
-    f32x4 acc[2][2];
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    // this thread's element e of a tile
+    auto at_a = [&](int e, int &mm, int &kk) {
+        const int idx = t + GT * e;
+        mm = AL::kFast ? idx / BK : idx % T;
+        kk = AL::kFast ? idx % BK : idx / T;
+    };
+    auto at_b = [&](int e, int &nn, int &kk) {
+        const int idx = t + GT * e;
+        nn = BL::kFast ? idx / BK : idx % T;
+        kk = BL::kFast ? idx % BK : idx / T;
+    };
+    // the next tile's elements are fetched before this tile's products and go to the other LDS buffer, one barrier a
+    // step: the short K ranges of a training step's products are bound by this latency
+    float ra[EA], rb[EB];
+    auto load = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kb; k0 < ke; k0 += BK) {
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < (BM * BK) / GT; ++e) {
-            const int idx = t + GT * e;
+        for (int e = 0; e < EA; ++e) {
             int mm, kk;
-            if constexpr (AL::kFast) {
-                mm = idx / BK;
-                kk = idx % BK;
-            } else {
-                kk = idx / BM;
-                mm = idx % BM;
-            }
-            As[kk][mm] = (k0 + kk < ke) ? al(m0 + mm, k0 + kk) : 0.f;
-            int nn, kk2;
-            if constexpr (BL::kFast) {
-                nn = idx / BK;
-                kk2 = idx % BK;
-            } else {
-                kk2 = idx / BN;
-                nn = idx % BN;
-            }
-            Bs[kk2][nn] = (k0 + kk2 < ke) ? bl(k0 + kk2, n0 + nn) : 0.f;
+            at_a(e, mm, kk);
+            ra[e] = (k0 + kk < ke) ? al(m0 + mm, k0 + kk) : 0.f;
         }
-        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EB; ++e) {
+            int nn, kk;
+            at_b(e, nn, kk);
+            rb[e] = (k0 + kk < ke) ? bl(k0 + kk, n0 + nn) : 0.f;
+        }
+    };
+    load(kb);
+    for (int k0 = kb, buf = 0; k0 < ke; k0 += BK, buf ^= 1) {
+#pragma unroll
+        for (int e = 0; e < EA; ++e) {
+            int mm, kk;
+            at_a(e, mm, kk);
+            As[buf][kk][mm] = ra[e];
+        }
+#pragma unroll
+        for (int e = 0; e < EB; ++e) {
+            int nn, kk;
+            at_b(e, nn, kk);
+            Bs[buf][kk][nn] = rb[e];
+        }
+        __syncthreads();  // this buffer is full; the other one's readers passed this barrier a step ago
+        if (k0 + BK < ke) load(k0 + BK);
 #pragma unroll
         for (int sub = 0; sub < BK / 4; ++sub) {
             const int kr = 4 * sub + (lane >> 4), c = lane & 15;
-            const float a0 = As[kr][wm + c], a1 = As[kr][wm + 16 + c];
-            const float b0 = Bs[kr][wn + c], b1 = Bs[kr][wn + 16 + c];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(As[buf][kr][wm + c], Bs[buf][kr][wn + c], acc, 0, 0, 0);
         }
     }
-    // lane l holds rows 4 (l / 16) + r, column l % 16 of each 16 x 16 tile
+    // lane l holds rows 4 (l / 16) + r, column l % 16 of its wave's tile
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r, n = n0 + wn + 16 * j + (lane & 15);
-                if (m < M && n < N) ep(m, n, z, acc[i][j][r]);
-            }
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + wm + 4 * (lane >> 4) + r, n = n0 + wn + (lane & 15);
+        if (m < M && n < N) ep(m, n, z, acc[r]);
+    }
+}
+
+// K range of each of about `splits` parts, and their number
+int split_length(int K, int splits) {
+    const int kspl = (K + splits - 1) / splits;
+    return kspl > kSplitStep ? (kspl + kSplitStep - 1) / kSplitStep * kSplitStep : kSplitStep;
+}
+int split_count(int K, int splits) {
+    const int kspl = split_length(K, splits);
+    return K > 0 ? (K + kspl - 1) / kspl : 1;
 }
 
 template <class AL, class BL, class EP>
 hipError_t gemm(int M, int N, int K, int splits, const AL &al, const BL &bl, const EP &ep, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (splits < 1) splits = 1;
-    int kspl = (K + splits - 1) / splits;
-    kspl = (kspl + BK - 1) / BK * BK;
-    if (kspl < BK) kspl = BK;
-    const int nz = K > 0 ? (K + kspl - 1) / kspl : 1;
-    hipLaunchKernelGGL((k_gemm<AL, BL, EP>), dim3((M + BM - 1) / BM, (N + BN - 1) / BN, nz), dim3(GT), 0, s, M, N, K,
+    const int nz = split_count(K, splits), kspl = split_length(K, splits);
+    hipLaunchKernelGGL((k_gemm<AL, BL, EP>), dim3((M + T - 1) / T, (N + T - 1) / T, nz), dim3(GT), 0, s, M, N, K,
                        kspl, al, bl, ep);
     return hipGetLastError();
 }
 
-// First layer, z = standardised inputs x W1 + b1, h = gelu(z), for 64 knots
-// by up to 128 hidden units per workgroup (4 waves, each 16 knots x 128
-// units as 8 MFMA tiles), K in steps of 32 through two LDS buffers.  A
-// thread gathers eight consecutive raw inputs of one knot per step through a
+// First layer, z = standardised inputs x W1 + b1, h = gelu(z), for MT knots
+// by up to 128 hidden units per workgroup (MT = 64: 4 waves, each 16 knots x
+// 128 units as 8 MFMA tiles; MT = 16, for few knots: each wave 16 knots x 32
+// units), K in steps of 32 through two LDS buffers.  A
+// thread gathers MT / 8 consecutive raw inputs of one knot per step through a
 // table of input offsets built in LDS at the start (D_k from its packed upper
 // triangle, L_k, gamma_k); the step's 32 means and inverse deviations go to
 // LDS beside the tile and standardise each A operand as it is read (features
@@ -226,19 +246,24 @@ hipError_t gemm(int M, int N, int K, int splits, const AL &al, const BL &bl, con
 // before this step's products, at clamped addresses and without branches,
 // so that no wait separates them.
 constexpr int kL1N = 128, kL1K = 32;
+// Knots up to which MT is 16: 64-knot workgroups give 8192 knots 128 of 256 CUs.  Measured with either, one nx 26
+// inference: 2048 knots 167 (MT = 64) and 87 us (16), 8192 knots 190 and 131, 12288 knots 190 and 201.
+constexpr int kL1Few = 8192;
 constexpr int kFeatL = 1, kFeatG = 2;  // input kinds in the table's top bits (0: D_k)
 constexpr int kL1MaxIn = 3136;         // table entries (the static tiles leave room for these)
 
-template <typename TM>
+template <typename TM, int MT>
 __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restrict__ W1, const float *__restrict__ b1,
                                                const float *__restrict__ mu, const float *__restrict__ isd, int nin,
                                                int H, float *__restrict__ Z, float *__restrict__ Hout) {
-    __shared__ float As[2][kL1K][BM + PADL];
+    constexpr int EA = MT / 8, NT = MT / 8;  // inputs per thread and step, tiles per wave
+    __shared__ float As[2][kL1K][MT + PADL];
     __shared__ float Bs[2][kL1K][kL1N + PADL];
     __shared__ float Ms[2][2][kL1K];  // mean, inverse deviation of the step's inputs
     __shared__ int foff[kL1MaxIn];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * kL1N;
+    const int m0 = blockIdx.x * MT, n0 = blockIdx.y * kL1N;
+    const int wr = MT == 64 ? 16 * w : 0, wc = MT == 64 ? 0 : 32 * w;  // this wave's rows and columns of the tile
     const int nx = s.nx, nn = nx * nx;
     for (int f = t; f < nin; f += GT) {
         int v;
@@ -252,8 +277,8 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
         }
         foff[f] = v;
     }
-    // this thread's A row and its eight inputs of each step
-    const int am = t >> 2, aq = (t & 3) * 8;
+    // this thread's A row and its inputs of each step
+    const int am = t / (kL1K / EA), aq = (t % (kL1K / EA)) * EA;
     const KnotInfo q = s.ki[min(m0 + am, s.M - 1)];  // rows past M: a valid knot (outputs not stored)
     const TM *src = (const TM *)s.B3 + q.blk;
     const double *gsrc = s.gamma + q.vec;
@@ -262,21 +287,21 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
     // inverse deviations)
     const int bk = t >> 3, bn = (t & 7) * 16;
     const int nlast = nin - 1;
-    f32x4 acc[8];
+    f32x4 acc[NT];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the next step's raw loads and their 0/1 weights: combined only when
     // they are stored, so that the loads stay in flight over this step's
     // products.  Both input loads are kept (weighted rather than selected) so
     // that the compiler issues them unconditionally; they read finite inputs
     // at valid addresses.
-    TM rd[8];
-    double rg[8];
-    float wd[8], wg[8], wb[4], rs, ws;
+    TM rd[EA];
+    double rg[EA];
+    float wd[EA], wg[EA], wb[4], rs, ws;
     f32x4 rb[4];
     auto load = [&](int k0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < EA; ++j) {
             const int fc = min(k0 + aq + j, nlast);
             const int e = foff[fc], kind = (int)((unsigned)e >> 30), o = e & 0x3fffffff;
             rd[j] = src[kind == kFeatG ? 0 : o];
@@ -300,7 +325,7 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
     load(0);
     for (int k0 = 0, buf = 0; k0 < nin; k0 += kL1K, buf ^= 1) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) As[buf][aq + j][am] = (float)rd[j] * wd[j] + (float)rg[j] * wg[j];
+        for (int j = 0; j < EA; ++j) As[buf][aq + j][am] = (float)rd[j] * wd[j] + (float)rg[j] * wg[j];
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -311,32 +336,23 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
 #pragma unroll
         for (int sub = 0; sub < kL1K / 4; ++sub) {
             const int kr = 4 * sub + (lane >> 4), c = lane & 15;
-            const float a = (As[buf][kr][16 * w + c] - Ms[buf][0][kr]) * Ms[buf][1][kr];
+            const float a = (As[buf][kr][wr + c] - Ms[buf][0][kr]) * Ms[buf][1][kr];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[buf][kr][16 * j + c], acc[j], 0, 0, 0);
+            for (int j = 0; j < NT; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[buf][kr][wc + 16 * j + c], acc[j], 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int m = m0 + 16 * w + 4 * (lane >> 4) + r, n = n0 + 16 * j + (lane & 15);
+            const int m = m0 + wr + 4 * (lane >> 4) + r, n = n0 + wc + 16 * j + (lane & 15);
             if (m < s.M && n < H) {
                 const float z = acc[j][r] + b1[n];
                 if (Z) Z[(int64_t)m * H + n] = z;
                 Hout[(int64_t)m * H + n] = gelu(z);
             }
         }
-}
-
-// number of K splits gemm() will use (the partial buffer holds that many)
-int split_count(int K, int splits) {
-    if (splits < 1) splits = 1;
-    int kspl = (K + splits - 1) / splits;
-    kspl = (kspl + BK - 1) / BK * BK;
-    if (kspl < BK) kspl = BK;
-    return K > 0 ? (K + kspl - 1) / kspl : 1;
 }
 
 // ------------------------------------------------------------ small kernels ---
@@ -357,24 +373,77 @@ __global__ void k_knot_info(const int32_t *knot_prob, const int64_t *koff, const
     out[m] = q;
 }
 
-// column sums of a row-major M x n matrix into out[0..n) (fixed order)
-__global__ __launch_bounds__(256) void k_colsum(const float *x, int M, int n, float *out) {
-    __shared__ float red[4][64];
-    const int c = threadIdx.x & 63, r = threadIdx.x >> 6, col = blockIdx.x * 64 + c;
-    float s = 0.f;
-    if (col < n)
-        for (int m = r; m < M; m += 4) s += x[(int64_t)m * n + col];
-    red[r][c] = s;
-    __syncthreads();
-    if (r == 0 && col < n) out[col] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+// The end of a backward pass: the weight gradients' partial sums over the K ranges (out = sum_z part[z]) and the bias
+// gradients, which are the column sums of the three row-major M x n output gradients, all in a fixed order.  The first
+// workgroups take the column sums, one wave to 16 columns (lane = column + 16 (row mod 4)), each a serial chain over
+// the rows that is bound by the latency of its loads: 128 rows' loads are in flight while the previous 128 are added.
+// (2300 rows: 108 us for each of the three with one load in flight, now 12 us for all of this kernel.)
+struct GradEnd {
+    const float *x[3];  // M x n
+    float *sum[3];
+    int n[3], first[4];  // columns; first 16-column group of each matrix
+    const float *part[3];
+    float *out[3];
+    int64_t cnt[3];
+    int M, nz, sums;  // sums: workgroups of column sums
+};
+
+constexpr int kSumRows = 32;  // loads of one lane per batch
+
+// a[q] as a selection: an index would read the kernel's arguments through the vector memory path, from the host
+template <typename T>
+__device__ __forceinline__ T pick(const T (&a)[3], int q) {
+    return q == 2 ? a[2] : q == 1 ? a[1] : a[0];
 }
 
-// out[i] = sum_z part[z * cnt + i] (fixed order)
-__global__ void k_sum_splits(const float *part, int nz, int64_t cnt, float *out) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < cnt; i += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void k_grad_end(GradEnd a) {
+    if ((int)blockIdx.x < a.sums) {
+        const int g = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+        if (g >= a.first[3]) return;
+        const int q = g >= a.first[2] ? 2 : g >= a.first[1] ? 1 : 0, n = pick(a.n, q);
+        const int first = q == 2 ? a.first[2] : q == 1 ? a.first[1] : 0;
+        const int col = (g - first) * 16 + (lane & 15), M = a.M;
+        const float *x = pick(a.x, q);
+        const int ofs = 4 * ((lane >> 4) * n + min(col, n - 1));
+        float v[2][kSumRows], s = 0.f;
+        // batch b: rows 4 (kSumRows b + e) + lane / 16; buffer loads give zeros for rows past M
+        auto load = [&](float(&d)[kSumRows], int b) {
+            const int64_t m0 = min((int64_t)4 * kSumRows * b, (int64_t)M);
+            const int rows = (int)min((int64_t)4 * kSumRows, M - m0);
+            const auto src = __builtin_amdgcn_make_buffer_rsrc((void *)(x + m0 * n), 0, 4 * rows * n, 0x00020000);
+#pragma unroll
+            for (int e = 0; e < kSumRows; ++e)
+                d[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, ofs + 16 * e * n, 0, 0));
+            __builtin_amdgcn_sched_barrier(0);  // else each load sinks to the add that uses it
+        };
+        auto add = [&](const float(&d)[kSumRows]) {
+#pragma unroll
+            for (int e = 0; e < kSumRows; ++e) s += d[e];
+        };
+        const int batches = (M + 4 * kSumRows - 1) / (4 * kSumRows);
+        load(v[0], 0);
+        for (int b = 0; b < batches; b += 2) {
+            load(v[1], b + 1);
+            add(v[0]);
+            load(v[0], b + 2);
+            add(v[1]);
+        }
+        const float s1 = __shfl(s, (lane & 15) + 16), s2 = __shfl(s, (lane & 15) + 32),
+                    s3 = __shfl(s, (lane & 15) + 48);
+        if (lane < 16 && col < n) pick(a.sum, q)[col] = (s + s1) + (s2 + s3);
+        return;
+    }
+    const int64_t c0 = a.cnt[0], c1 = c0 + a.cnt[1], c2 = c1 + a.cnt[2];
+    for (int64_t i = (int64_t)(blockIdx.x - a.sums) * 256 + threadIdx.x; i < c2;
+         i += (int64_t)(gridDim.x - a.sums) * 256) {
+        const int q = i >= c1 ? 2 : i >= c0 ? 1 : 0;
+        const int64_t o = i - (q == 2 ? c1 : q == 1 ? c0 : 0);
+        const float *part = pick(a.part, q) + o;
+        const int64_t cnt = pick(a.cnt, q);
         float s = 0.f;
-        for (int z = 0; z < nz; ++z) s += part[z * cnt + i];
-        out[i] = s;
+#pragma unroll 8
+        for (int z = 0; z < a.nz; ++z) s += part[z * cnt];
+        pick(a.out, q)[o] = s;
     }
 }
 
@@ -520,8 +589,13 @@ hipError_t forward_t(const FeatSrc &f, const NetView &w, const float *mu, const 
                      float *H1, float *Z2, float *H2, float *O, double *lam, hipStream_t s) {
     hipError_t e;
     if (w.nin <= kL1MaxIn && w.H % 4 == 0) {
-        hipLaunchKernelGGL(k_layer1<TM>, dim3((f.M + BM - 1) / BM, (w.H + kL1N - 1) / kL1N), dim3(GT), 0, s, f, w.W1,
-                           w.b1, mu, isd, w.nin, w.H, Z1, H1);
+        const int cols = (w.H + kL1N - 1) / kL1N;
+        if (f.M <= kL1Few)
+            hipLaunchKernelGGL((k_layer1<TM, 16>), dim3((f.M + 15) / 16, cols), dim3(GT), 0, s, f, w.W1, w.b1, mu,
+                               isd, w.nin, w.H, Z1, H1);
+        else
+            hipLaunchKernelGGL((k_layer1<TM, 64>), dim3((f.M + 63) / 64, cols), dim3(GT), 0, s, f, w.W1, w.b1, mu,
+                               isd, w.nin, w.H, Z1, H1);
         if ((e = hipGetLastError())) return e;
     } else {
         FeatA<TM> fa{f, mu, isd, w.nin};
@@ -535,39 +609,35 @@ hipError_t forward_t(const FeatSrc &f, const NetView &w, const float *mu, const 
                 EpOut{w.b3, O, w.nx, f.ki, lam, ys}, s);
 }
 
-// weight gradient op(A)^T-style product with a K split over the knots,
-// summed into dst
-template <class AL, class BL>
-hipError_t wgrad(int M, int N, int K, const AL &al, const BL &bl, float *split, int splits, float *dst,
-                 hipStream_t s) {
-    const int nz = split_count(K, splits);
-    hipError_t e = gemm(M, N, K, splits, al, bl, EpStore{split, N, (int64_t)M * N}, s);
-    if (e) return e;
-    hipLaunchKernelGGL(k_sum_splits, dim3(grid_for((int64_t)M * N, 256)), dim3(256), 0, s, split, nz,
-                       (int64_t)M * N, dst);
-    return hipGetLastError();
-}
-
 template <typename TM>
 hipError_t backward_t(const FeatSrc &f, const NetView &w, const float *mu, const float *isd, const float *Z1,
                       const float *H1, const float *Z2, const float *H2, const float *dO, float *dZ2, float *dZ1,
-                      float *grad, float *split, int splits, hipStream_t s) {
+                      float *grad, float *split, hipStream_t s) {
     const int M = f.M, H = w.H, nx = w.nx, nin = w.nin;
     float *gW1 = grad, *gb1 = gW1 + (int64_t)nin * H, *gW2 = gb1 + H, *gb2 = gW2 + (int64_t)H * H, *gW3 = gb2 + H,
           *gb3 = gW3 + (int64_t)H * nx;
+    // weight gradients over kSplits ranges of the knots, summed at the end with the bias gradients
+    GradEnd end{{dZ1, dZ2, dO}, {gb1, gb2, gb3}, {H, H, nx}, {}, {}, {gW1, gW2, gW3},
+                {(int64_t)nin * H, (int64_t)H * H, (int64_t)H * nx}, M, split_count(M, kSplits), 0};
+    for (int q = 0; q < 3; ++q) {
+        end.first[q + 1] = end.first[q] + (end.n[q] + 15) / 16;
+        end.part[q] = split;
+        split += kSplits * end.cnt[q];
+    }
+    end.sums = (end.first[3] + 3) / 4;
+    auto part = [&](int q, int ld) { return EpStore{(float *)end.part[q], ld, end.cnt[q]}; };
     hipError_t e;
     // layer 3: dW3 = H2^T dO, db3 = colsum dO, dZ2 = (dO W3^T) * gelu'(Z2)
-    if ((e = wgrad(H, nx, M, ColA{H2, H, H, M}, RowB{dO, nx, M, nx}, split, splits, gW3, s))) return e;
-    hipLaunchKernelGGL(k_colsum, dim3((nx + 63) / 64), dim3(256), 0, s, dO, M, nx, gb3);
+    if ((e = gemm(H, nx, M, kSplits, ColA{H2, H, H, M}, RowB{dO, nx, M, nx}, part(2, nx), s))) return e;
     if ((e = gemm(M, H, nx, 1, RowA{dO, nx, M, nx}, ColB{w.W3, nx, nx, H}, EpGeluBack{Z2, dZ2, H}, s))) return e;
     // layer 2
-    if ((e = wgrad(H, H, M, ColA{H1, H, H, M}, RowB{dZ2, H, M, H}, split, splits, gW2, s))) return e;
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(256), 0, s, dZ2, M, H, gb2);
+    if ((e = gemm(H, H, M, kSplits, ColA{H1, H, H, M}, RowB{dZ2, H, M, H}, part(1, H), s))) return e;
     if ((e = gemm(M, H, H, 1, RowA{dZ2, H, M, H}, ColB{w.W2, H, H, H}, EpGeluBack{Z1, dZ1, H}, s))) return e;
     // layer 1 (inputs re-read from the stored blocks)
     FeatAT<TM> ft{FeatA<TM>{f, mu, isd, nin}};
-    if ((e = wgrad(nin, H, M, ft, RowB{dZ1, H, M, H}, split, splits, gW1, s))) return e;
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(256), 0, s, dZ1, M, H, gb1);
+    if ((e = gemm(nin, H, M, kSplits, ft, RowB{dZ1, H, M, H}, part(0, H), s))) return e;
+    hipLaunchKernelGGL(k_grad_end, dim3(end.sums + grid_for(end.cnt[0] + end.cnt[1] + end.cnt[2], 256)), dim3(256),
+                       0, s, end);
     return hipGetLastError();
 }
 
@@ -627,10 +697,10 @@ hipError_t launch_mlp_loss(const FeatSrc &f, const float *O, float y_scale, cons
 
 hipError_t launch_mlp_backward(const FeatSrc &f, const NetView &w, const float *mu, const float *inv_sd,
                                const float *Z1, const float *H1, const float *Z2, const float *H2, const float *dO,
-                               float *dZ2, float *dZ1, float *grad, float *split, int splits, hipStream_t s) {
+                               float *dZ2, float *dZ1, float *grad, float *split, hipStream_t s) {
     if (f.M <= 0) return hipErrorInvalidValue;
-    return f.fp32 ? backward_t<float>(f, w, mu, inv_sd, Z1, H1, Z2, H2, dO, dZ2, dZ1, grad, split, splits, s)
-                  : backward_t<double>(f, w, mu, inv_sd, Z1, H1, Z2, H2, dO, dZ2, dZ1, grad, split, splits, s);
+    return f.fp32 ? backward_t<float>(f, w, mu, inv_sd, Z1, H1, Z2, H2, dO, dZ2, dZ1, grad, split, s)
+                  : backward_t<double>(f, w, mu, inv_sd, Z1, H1, Z2, H2, dO, dZ2, dZ1, grad, split, s);
 }
 
 hipError_t launch_adam(float *theta, const float *grad, float *m, float *v, int64_t n, float lr, float beta1,

@@ -22,7 +22,7 @@ struct ssp_mlp {
     float ys = 1.0f;
     int64_t t = 0;  // Adam steps taken
     // scratch sized for `cap` knots
-    int cap = 0, splits = 16;
+    int cap = 0;
     ssp::KnotInfo *ki = nullptr;
     float *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *dZ1 = nullptr, *dZ2 = nullptr;
     float *O = nullptr, *E = nullptr, *R = nullptr, *dO = nullptr, *split = nullptr;
@@ -50,12 +50,12 @@ ssp_status ensure_scratch(ssp_mlp *m, int knots) {
     SSP_HIP(hipDeviceSynchronize());
     free_scratch(m);
     const size_t M = (size_t)knots, H = m->H, nx = m->nx;
-    const size_t big = std::max({(size_t)m->nin * H, H * H, H * nx});
+    const size_t weights = (size_t)m->nin * H + H * H + H * nx;
     const size_t npart = std::max((M * nx + 255) / 256 + 1, (size_t)2 * 64 * (m->nin + nx));
     bool ok = dalloc(&m->ki, M) == hipSuccess;
     for (float **p : {&m->Z1, &m->H1, &m->Z2, &m->H2, &m->dZ1, &m->dZ2}) ok = ok && dalloc(p, M * H) == hipSuccess;
     for (float **p : {&m->O, &m->E, &m->R, &m->dO}) ok = ok && dalloc(p, M * nx) == hipSuccess;
-    ok = ok && dalloc(&m->split, (size_t)m->splits * big) == hipSuccess;
+    ok = ok && dalloc(&m->split, ssp::kSplits * weights) == hipSuccess;
     ok = ok && dalloc(&m->part, npart) == hipSuccess;
     if (!ok) {
         free_scratch(m);
@@ -293,7 +293,7 @@ ssp_status ssp_mlp_loss_grad(ssp_mlp *m, ssp_batch *b, int32_t p0, int32_t p1, c
     SSP_HIP(ssp::launch_mlp_forward(f, w, m->mu, m->isd, m->ys, m->Z1, m->H1, m->Z2, m->H2, m->O, nullptr, s));
     SSP_HIP(ssp::launch_mlp_loss(f, m->O, m->ys, lambda_star, p1 - p0, m->E, m->R, m->dO, m->part, m->loss, s));
     SSP_HIP(ssp::launch_mlp_backward(f, w, m->mu, m->isd, m->Z1, m->H1, m->Z2, m->H2, m->dO, m->dZ2, m->dZ1, m->grad,
-                                     m->split, m->splits, s));
+                                     m->split, s));
     if (loss) SSP_HIP(hipMemcpyAsync(loss, m->loss, sizeof(double), hipMemcpyDeviceToDevice, s));
     return SSP_OK;
 }

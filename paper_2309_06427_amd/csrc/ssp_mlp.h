@@ -56,11 +56,13 @@ hipError_t launch_mlp_forward(const FeatSrc &f, const NetView &w, const float *m
 hipError_t launch_mlp_loss(const FeatSrc &f, const float *O, float y_scale, const double *lam_star, int nprob,
                            float *E, float *R, float *dO, double *part, double *loss, hipStream_t s);
 
+constexpr int kSplits = 16;  // ranges of the knots whose weight gradients are summed apart
+
 // Backward pass into grad (parameter layout); dZ2, dZ1: M x H scratch;
-// split: K-split partials, 'splits' * (nin * H) floats.
+// split: the ranges' weight gradients, kSplits * (nin * H + H * H + H * nx) floats.
 hipError_t launch_mlp_backward(const FeatSrc &f, const NetView &w, const float *mu, const float *inv_sd,
                                const float *Z1, const float *H1, const float *Z2, const float *H2, const float *dO,
-                               float *dZ2, float *dZ1, float *grad, float *split, int splits, hipStream_t s);
+                               float *dZ2, float *dZ1, float *grad, float *split, hipStream_t s);
 
 hipError_t launch_adam(float *theta, const float *grad, float *m, float *v, int64_t n, float lr, float beta1,
                        float beta2, float eps, float bc1, float bc2, hipStream_t s);

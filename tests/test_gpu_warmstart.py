@@ -262,3 +262,30 @@ def test_training_labels_match_the_oracle():
         err = np.linalg.norm(lab[b.off_v[i]:b.off_v[i + 1]] - ref) / np.linalg.norm(ref)
         assert err <= dense.kappa(D, L) * 1e-10, (i, err)
     db.close()
+
+
+@pytest.mark.parametrize("knots", [1, 127, 128, 129, 256, 385])
+def test_gradient_at_the_edges_of_the_row_batches(knots):
+    """Bias and weight gradients of one problem whose length meets and misses the kernels' batches of 128 knots."""
+    nx, H = 5, 16
+    b, db, probs, lam_star = _pool(nx, 1, 3, N_range=(knots, knots))
+    net, theta = _net(nx, H, 6)
+    loss = net.loss_grad(db, 0, 1, lam_star)
+    mu, isd, ys = net.get_scaling()
+    ref_loss, ref_g = mlp.loss_and_grad(theta, probs, mu.astype(np.float64), isd.astype(np.float64), ys, nx, H)
+    assert abs(float(loss) - ref_loss) <= 2e-4 * ref_loss
+    assert rel(net.get_grad(), ref_g) < 2e-4
+
+
+@pytest.mark.parametrize("nx,H", [(5, 16), (6, 144)])
+@pytest.mark.parametrize("P", [128, 129])
+def test_prediction_is_the_same_in_small_and_large_batches(nx, H, P):
+    """A knot's guess does not depend on how many knots share its launch: 64 a problem, so 8192 and 8256 in all."""
+    from paper_2309_06427_amd import solver
+    b = inputs.batch(P, 5, N_range=(64, 64), nx_choices=(nx,))
+    db = solver.DeviceBatch(b)
+    db.build("sym", "fp32_refine64")
+    df = solver.DeviceBatch(inputs.batch(P, 5, N_range=(64, 64), nx_choices=(nx,), first=P - 3, count=3))
+    df.build("sym", "fp32_refine64")
+    net, _ = _net(nx, H, 8)
+    assert torch.equal(net.predict(db)[-3 * 64 * nx:], net.predict(df))
