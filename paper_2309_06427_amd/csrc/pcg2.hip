@@ -82,7 +82,15 @@ __host__ __device__ inline int pcg2_knots_per_step(int nx, int block, int lds_by
 // loads) and the six recurrence vectors of this thread's lead row.  Every
 // load is issued unconditionally (surplus slots re-read the step's first
 // vector), so the compiler can count outstanding loads and the compute
-// phases never wait on them.
+// phases never wait on them.  The loads go out in kParts parts between the
+// phases of the current step: issued at once they fill the memory pipeline,
+// and every wave stands there while nothing is computed.  Their addresses are
+// formed where they are used: kept from step to step they were spilled, and a
+// spilled value's reload waits for the loads issued before it.  (FP64, nx 26,
+// 128 knots from HBM, 512 threads: one pass 330 thousand cycles before, 255
+// now, of which 20 to 60 in each of store, B, C, D and E, bound by the LDS
+// reads of 7 matrix and 7 vector terms a row; FP64 solve of 1024 problems of
+// condition 1e6: 69.1 ms before, 59.4 now.)
 template <typename TM, int BLOCK>
 struct Prefetch {
     using VT = typename Vec16<TM>::T;
@@ -92,27 +100,35 @@ struct Prefetch {
     TM vec[6];       // u, w, p, s, x, r of this thread's lead row
     double res = 0;  // init pass: the FP64 residual of that row instead
 
+    static constexpr int kParts = 4;
+
+    // part PART of the loads of the step of kc knots from k0
+    template <int PART>
     __device__ __forceinline__ void issue(const TM *B3, int k0, int kc, int ks, bool init, int lead_row,
                                           const double *r64, const Vecs<TM> vs) {
+        constexpr int m0 = PART * kPF / kParts, m1 = (PART + 1) * kPF / kParts;
         // the step's D, L, D^-1 blocks: one contiguous chunk of kc knot strides
         const int nvec = kc * ks / V;
         const VT *src = (const VT *)(B3 + (int64_t)k0 * ks);
-        static_for<0, kPF>([&](auto mc) {
+        const int t = fresh(threadIdx.x);
+        static_for<m0, m1>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            int q = threadIdx.x + m * BLOCK;
+            int q = t + m * BLOCK;
             if (q >= nvec) q = 0;
             reg[m] = src[q];
         });
-        const int row = lead_row >= 0 ? lead_row : 0;
-        if (init) {
-            res = r64[row];
-        } else {
-            vec[0] = vs.u[row];
-            vec[1] = vs.w[row];
-            vec[2] = vs.p[row];
-            vec[3] = vs.s[row];
-            vec[4] = vs.x[row];
-            vec[5] = vs.r[row];
+        if constexpr (PART == 0) {
+            const int row = fresh(lead_row >= 0 ? lead_row : 0);
+            if (init) {
+                res = r64[row];
+            } else {
+                vec[0] = vs.u[row];
+                vec[1] = vs.w[row];
+                vec[2] = vs.p[row];
+                vec[3] = vs.s[row];
+                vec[4] = vs.x[row];
+                vec[5] = vs.r[row];
+            }
         }
     }
 
@@ -180,70 +196,66 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
     // s / sp: block-ring slots of k / k + 1
     auto s_row = [&](const TI *xb, int sx, int sxm, int sxp, int s, int sp, bool diag) -> TI {
         TI y = TI(0);
-        if (diag) y += sym_dot<NX>(rD + s * ss, i, xb + sx * nxp, nx);        // D_k (packed)
-        if (sxm >= 0) y += row_dot<NX>(rL + s * ss, i, xb + sxm * nxp, nx);   // row i of L_k
-        if (sxp >= 0) y += col_dot<NX>(rL + sp * ss, i, xb + sxp * nxp, nx);  // column i of L_{k+1}
+        const int r = fresh(i);
+        if (diag) y += sym_dot<NX>(rD + s * ss, r, xb + sx * nxp, nx);        // D_k (packed)
+        if (sxm >= 0) y += row_dot<NX>(rL + s * ss, r, xb + sxm * nxp, nx);   // row i of L_k
+        if (sxp >= 0) y += col_dot<NX>(rL + sp * ss, r, xb + sxp * nxp, nx);  // column i of L_{k+1}
         return y;
     };
 
     // results of the previous step, written at the start of the next one
-    TI oP = TI(0), oS = TI(0), oX = TI(0), oR = TI(0), oU = TI(0), oW = TI(0);
-    int rowA = -1, rowU = -1, rowW = -1;
+    TI oU = TI(0), oW = TI(0);
+    int rowU = -1, rowW = -1;
 
     Prefetch<TM, BLOCK> pf;
     const int nsteps = (N + C - 1) / C;
     auto lead_row = [&](int k0, int kc) { return (lane_ok && kme < kc) ? (k0 + kme) * nx + i : -1; };
-    pf.issue(B3, 0, min(C, N), ks, init, lead_row(0, min(C, N)), r64, vsrc);
+    static_for<0, 4>([&](auto part) {
+        pf.template issue<decltype(part)::value>(B3, 0, min(C, N), ks, init, lead_row(0, min(C, N)), r64, vsrc);
+    });
     int sb = 0, sbu = 0;  // ring slots of knot k0
     for (int c = 0; c < nsteps; ++c) {
         const int k0 = c * C, kc = min(C, N - k0), k1 = k0 + kc;
         const bool last = k1 == N;
         __syncthreads();  // every reader of the slots about to be refilled is done
         pf.store(ring, kc, sb, ks, R, vu + RU * nxp);
-        TM cur[6];
-#pragma unroll
-        for (int v = 0; v < 6; ++v) cur[v] = pf.vec[v];
-        const double res = pf.res;
-        // write back the previous step's rows before the next loads go out
-        if (rowA >= 0) {
-            if (!init) {
-                Pv[rowA] = oP;
-                Sv[rowA] = oS;
-            }
-            Xv[rowA] = oX;
-            Rv[rowA] = oR;
-        }
+        // the rows that the previous step finished, then A: recurrence updates on the lead rows, written before the
+        // next loads go out
         if (rowU >= 0) Uv[rowU] = oU;
         if (rowW >= 0) Wv[rowW] = oW;
-        rowA = rowU = rowW = -1;
-        if (!last) pf.issue(B3, k1, min(C, N - k1), ks, init, lead_row(k1, min(C, N - k1)), r64, vsrc);
-
+        rowU = rowW = -1;
         const bool lead = lane_ok && kme < kc;
         const int sl = slot_of(sb, kme, R);
-        // A: recurrence updates on the lead rows
         if (lead) {
+            const int row = (k0 + kme) * nx + i;
             TI r;
             if (init) {
-                r = (TI)(res * inv_s);
-                oX = TI(0);
+                r = (TI)(pf.res * inv_s);
+                Xv[row] = TI(0);
             } else {
-                const TI pv = first ? cur[0] : cur[0] + beta * cur[2];
-                const TI sv = first ? cur[1] : cur[1] + beta * cur[3];
-                oP = pv;
-                oS = sv;
-                oX = cur[4] + alpha * pv;
-                r = cur[5] - alpha * sv;
+                const TI pv = first ? pf.vec[0] : pf.vec[0] + beta * pf.vec[2];
+                const TI sv = first ? pf.vec[1] : pf.vec[1] + beta * pf.vec[3];
+                Pv[row] = pv;
+                Sv[row] = sv;
+                Xv[row] = pf.vec[4] + alpha * pv;
+                r = pf.vec[5] - alpha * sv;
             }
-            oR = r;
-            rowA = (k0 + kme) * nx + i;
+            Rv[row] = r;
             vr[sl * nxp + i] = r;
             d.rho += r * r;
         }
+        auto issue = [&](auto part) {
+            if (!last)
+                pf.template issue<decltype(part)::value>(B3, k1, min(C, N - k1), ks, init,
+                                                         lead_row(k1, min(C, N - k1)), r64, vsrc);
+        };
+        issue(std::integral_constant<int, 0>{});
         __syncthreads();  // the ring blocks stored above come from every wave
+        issue(std::integral_constant<int, 1>{});
         // B: y = D^-1 r on the lead knots (u itself for block-Jacobi)
         if (lead) {
             const TI *rk = vr + sl * nxp;
-            const TI y = sym_dot<NX>(rDi + sl * ss, i, rk, nx);
+            const TI y = sym_dot<NX>(rDi + sl * ss, fresh(i), rk, nx);
             if (bj) {
                 vu[slot_of(sbu, kme, RU) * nxp + i] = y;
                 oU = y;
@@ -254,6 +266,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
             }
         }
         __syncthreads();
+        issue(std::integral_constant<int, 2>{});
         int wlo, whi;  // knots that receive w in this step
         if (!bj) {
             // C: t = O y one knot behind the lead; D: u = y - c D^-1 t (same wave)
@@ -267,11 +280,12 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
                 vt[s * nxp + i] = s_row(vy, s, sm, sp, s, sp, false);
             }
             wave_sync();
+            issue(std::integral_constant<int, 3>{});
             for (int kk = kme; kk < thi - tlo; kk += group) {
                 if (!lane_ok) break;
                 const int k = tlo + kk, dk = k - k0;
                 const int s = slot_of(sb, dk, R);
-                const TI z = sym_dot<NX>(rDi + s * ss, i, vt + s * nxp, nx);
+                const TI z = sym_dot<NX>(rDi + s * ss, fresh(i), vt + s * nxp, nx);
                 const TI u = vy[s * nxp + i] - c2 * z;
                 vu[slot_of(sbu, dk, RU) * nxp + i] = u;
                 d.gam += vr[s * nxp + i] * u;
@@ -286,6 +300,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
             wlo = max(k0 - 2, 0);
             whi = last ? N : k1 - 2;
         } else {
+            issue(std::integral_constant<int, 3>{});
             wlo = max(k0 - 1, 0);
             whi = last ? N : k1 - 1;
         }
@@ -310,14 +325,6 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
         if (sb >= R) sb -= R;
         sbu += C;
         if (sbu >= RU) sbu -= RU;
-    }
-    if (rowA >= 0) {
-        if (!init) {
-            Pv[rowA] = oP;
-            Sv[rowA] = oS;
-        }
-        Xv[rowA] = oX;
-        Rv[rowA] = oR;
     }
     if (rowU >= 0) Uv[rowU] = oU;
     if (rowW >= 0) Wv[rowW] = oW;

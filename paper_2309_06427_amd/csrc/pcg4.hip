@@ -130,13 +130,6 @@ __device__ __forceinline__ float dot_bcast(const float (&a)[NX], const float (&x
     return s0 + s1;
 }
 
-// A copy of a lane's index that the compiler takes for a new value: what follows from it is computed again where it
-// is used instead of being kept in registers across the passes.
-__device__ __forceinline__ int fresh(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 __device__ __forceinline__ void pin(float v) { asm volatile("" ::"v"(v)); }
 
 template <int NX>
@@ -162,6 +155,7 @@ __device__ __forceinline__ Place4 place4(int N) {
     return z;
 }
 
+using ssp::fresh;
 __device__ __forceinline__ Place4 fresh(Place4 z) {
     z.g = fresh(z.g);
     z.p = fresh(z.p);

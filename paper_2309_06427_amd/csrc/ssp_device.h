@@ -44,6 +44,13 @@ __device__ __forceinline__ double uniform(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// A copy of a lane's index that the compiler takes for a new value: what follows from it is computed again where it
+// is used instead of being kept in registers across the passes.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Butterfly sum over the 64 lanes of a wavefront.  Every lane ends with the
 // same bits: each stage adds the same two operands on both partner lanes.
 // All stages are register moves between lanes (half and quarter swaps, then

@@ -255,10 +255,10 @@ __device__ __forceinline__ ResNorms residual_pass(int N, int C, const TM *__rest
     double lamv = 0.0;
 
     auto issue = [&](int k0, int kc) {
-        const int nvec = kc * VPK;
+        const int nvec = kc * VPK, t = fresh(threadIdx.x);
         static_for<0, KP>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            int q = threadIdx.x + m * BLOCK;
+            int q = t + m * BLOCK;
             if (q >= nvec) q = 0;  // surplus slots re-read the first vector
             const int kk = q / VPK, e = (q - kk * VPK) * V;
             const int64_t k = k0 + kk;
