@@ -18,9 +18,9 @@
 // The step reads each knot's blocks once and does nx^2 multiply-adds per
 // block, so it is bound by HBM.  For nx = 6, 14, 26 with nu <= nx / 2 a wave
 // takes 8, 4 or 1 consecutive knots of one problem (8 or 16 lanes per knot
-// for the small sizes), first copies all their blocks into LDS (contiguous
-// wave-wide loads, all issued before the first LDS write) and multiplies
-// from there; a lane reading its own matrix row from HBM would touch up to
+// for the small sizes), loads all their blocks (contiguous wave-wide loads,
+// all issued before the first LDS write), copies them into LDS in two phases
+// and multiplies from there; a lane reading its own matrix row from HBM would touch up to
 // nx cache lines per load instruction.  Other sizes run one generic kernel
 // that reads the rows from HBM directly.
 #include "ssp_device.h"
@@ -76,6 +76,9 @@ __device__ __forceinline__ double col_mv(const double *__restrict__ M, int i, in
 
 // ---- staged kernels (compiled state sizes) ----
 
+// doubles of the wave-wide copies that cover n
+constexpr int ranges(int n) { return (n + 63) / 64 * 64; }
+
 template <int NX>
 struct KktGeo {
     static constexpr int NUM = NX / 2;  // largest control size of the class
@@ -83,13 +86,19 @@ struct KktGeo {
     // knots per wave (consecutive knots of one problem) and lanes per knot
     static constexpr int KP = NX <= 8 ? 8 : NX <= 16 ? 4 : 1;
     static constexpr int RL = 64 / KP;
-    // nx x nx blocks sit in LDS with an odd row stride (in doubles), so
-    // that lanes reading their own rows hit distinct banks
-    static constexpr int LD = NX | 1;
-    static constexpr int NNP = NX * LD;
-    // LDS doubles per wave: KP + 1 Q^-1 blocks, KP blocks of A, B, R^-1,
-    // three vectors of RL entries per knot
-    static constexpr int PW = (2 * KP + 1) * NNP + KP * (NX * NUM + NUM * NUM) + 3 * 64;
+    // Blocks sit in LDS as in memory.  A lane reads its own row: with a row stride of NX doubles the rows of a block
+    // start in distinct banks (NX 6, 14) or in pairs (NX 26).
+    static constexpr int LD = NX;
+    // LDS doubles per wave: the blocks of one of a kernel's two phases at a time (the other phase's wait in
+    // registers) and three vectors of RL entries per knot.  Right-hand side: KP + 1 Q^-1 and KP R^-1 blocks, then A
+    // and B; recovery: A and B, then Q^-1 and R^-1.  What bounds both is HBM through the loads in flight, so the
+    // waves per CU: with all of a wave's blocks in LDS at once and an address register for each load 7, now 11 and
+    // 16 (nx 26, 1365 problems of 32 to 256 knots: right-hand side 711 us, now 617; recovery 601, now 550, at 5.6
+    // TB/s; the right-hand side reads each Q^-1 twice, mostly from L2).
+    static constexpr int SA = ranges(KP * NN), SB = ranges(KP * NX * NUM), SR = ranges(KP * NUM * NUM);
+    static constexpr int SQ1 = ranges((KP + 1) * NN), SQ = ranges(KP * NN);
+    static constexpr int PR = (SQ1 + SR > SA + SB ? SQ1 + SR : SA + SB) + 3 * 64;
+    static constexpr int PX = (SQ + SR > SA + SB ? SQ + SR : SA + SB) + 3 * 64;
     static constexpr int WAVES = KP == 8 ? 4 : 1;  // waves per workgroup
 };
 
@@ -105,43 +114,40 @@ __device__ __forceinline__ int64_t xcd_block() {
 template <int MAXN>
 constexpr int regs_for() { return (MAXN + 63) / 64; }
 
-// n <= MAXN contiguous doubles from src into registers, lane ln taking
-// elements ln, ln + 64, ...; indices past n repeat element n - 1 (src must
-// hold at least one element, also for n = 0)
+// n <= MAXN contiguous doubles of src, then zeros up to ranges(MAXN), into registers: lane ln takes elements ln,
+// ln + 64, ....  The buffer's bounds check gives the zeros, and the loads share a few address registers.
 template <int MAXN>
 __device__ __forceinline__ void ld_range(double (&v)[regs_for<MAXN>()], const double *__restrict__ src, int n,
                                          int ln) {
-    const int last = max(n, 1) - 1;
+    const uint64_t p = (uint64_t)src;  // uniform, said so
+    const uint64_t u = ((uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) |
+                       (unsigned)__builtin_amdgcn_readfirstlane((int)p);
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void *)u, 0, __builtin_amdgcn_readfirstlane(8 * n), 0x00020000);
+    const int ofs = 8 * ln;
 #pragma unroll
-    for (int t = 0; t < regs_for<MAXN>(); ++t) v[t] = src[min(t * 64 + ln, last)];
+    for (int t = 0; t < regs_for<MAXN>(); ++t)
+        v[t] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, ofs + 512 * t, 0, 0));
 }
 
 template <int MAXN>
-__device__ __forceinline__ void st_range(double *dst, const double (&v)[regs_for<MAXN>()], int n, int ln) {
+__device__ __forceinline__ void st_range(double *dst, const double (&v)[regs_for<MAXN>()], int ln) {
 #pragma unroll
-    for (int t = 0; t < regs_for<MAXN>(); ++t) {
-        const int e = t * 64 + ln;
-        if (e < n) dst[e] = v[t];
-    }
+    for (int t = 0; t < regs_for<MAXN>(); ++t) dst[t * 64 + ln] = v[t];
 }
 
-// the same for consecutive row-major blocks of NC columns, stored with row
-// stride LD (element e at e + (e / NC) (LD - NC))
-template <int MAXN, int NC, int LD>
-__device__ __forceinline__ void st_rows(double *dst, const double (&v)[regs_for<MAXN>()], int n, int ln) {
-#pragma unroll
-    for (int t = 0; t < regs_for<MAXN>(); ++t) {
-        const int e = t * 64 + ln;
-        if (e < n) dst[e + (e / NC) * (LD - NC)] = v[t];
-    }
-}
+// Terms of a dot product whose LDS reads are in flight together: the next ones' addresses are made to depend on the
+// sums, else all reads are issued first and their registers (256 a wave) leave one wave per SIMD.
+constexpr int kTerms = 8;
 
 // sum_j M[i][j] v[j], j < NC (compile time), M row-major with row stride ld in LDS
 template <int NC>
 __device__ __forceinline__ double lds_row(const double *M, int ld, int i, const double *v) {
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) (j & 1 ? s1 : s0) += M[i * ld + j] * v[j];
+    for (int j = 0; j < NC; ++j) {
+        (j & 1 ? s1 : s0) += M[i * ld + j] * v[j];
+        if (j % kTerms == kTerms - 1) asm("" : "+v"(i) : "v"(s0), "v"(s1));
+    }
     return s0 + s1;
 }
 
@@ -150,8 +156,10 @@ template <int NC>
 __device__ __forceinline__ double lds_row_n(const double *M, int ld, int i, const double *v, int m) {
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-    for (int j = 0; j < NC; ++j)
+    for (int j = 0; j < NC; ++j) {
         if (j < m) (j & 1 ? s1 : s0) += M[i * ld + j] * v[j];
+        if (j % kTerms == kTerms - 1) asm("" : "+v"(i) : "v"(s0), "v"(s1));
+    }
     return s0 + s1;
 }
 
@@ -160,7 +168,10 @@ template <int NR>
 __device__ __forceinline__ double lds_col(const double *M, int ld, int i, const double *v) {
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-    for (int j = 0; j < NR; ++j) (j & 1 ? s1 : s0) += M[j * ld + i] * v[j];
+    for (int j = 0; j < NR; ++j) {
+        (j & 1 ? s1 : s0) += M[j * ld + i] * v[j];
+        if (j % kTerms == kTerms - 1) asm("" : "+v"(i) : "v"(s0), "v"(s1));
+    }
     return s0 + s1;
 }
 
@@ -175,8 +186,8 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
                                                                      const double *q, const double *r,
                                                                      const double *c, double *gamma) {
     using G = KktGeo<NX>;
-    constexpr int NN = G::NN, NUM = G::NUM, LD = G::LD, NNP = G::NNP, KP = G::KP, RL = G::RL;
-    __shared__ double sm[G::WAVES][G::PW];
+    constexpr int NN = G::NN, NUM = G::NUM, LD = G::LD, KP = G::KP, RL = G::RL;
+    __shared__ double sm[G::WAVES][G::PR];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln = threadIdx.x & 63;
     // item j + 1 reads the last Q^-1 block of item j: neighbours share an XCD
     const int64_t g = xcd_block() * G::WAVES + w;
@@ -185,34 +196,31 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
     const int k0 = it.k0, N = it.N, nu = it.nu;
     const int nk = min(KP, N - k0);
     const int64_t ov = it.ov, ou = it.ou, onn = it.onn;
-    // blocks in LDS: Q^-1_{k0-1+j} in Q slot j (j = 0 .. nk), and A_{k-1},
-    // B_{k-1}, R^-1_{k-1} of knot k = k0 + s in slot s; k0 = 0 has no Q
-    // slot 0 and no slot 0 of the others
-    const int h = k0 > 0 ? 0 : 1;         // first slot present
+    // blocks in LDS: Q^-1_{k-1} in Q slot s - h and Q^-1_k in the next, and A_{k-1}, B_{k-1}, R^-1_{k-1} of knot
+    // k = k0 + s in slot s - h; h = 1 where the item starts at knot 0, which has no predecessor
+    const int h = k0 > 0 ? 0 : 1;
     const int na = nk - h;                // knots k >= 1 among the item
     const int nb = nu > 0 ? na * NX * nu : 0, nr = nu > 0 ? na * nu * nu : 0;
-    double *sQ = sm[w], *sA = sQ + (KP + 1) * NNP, *sB = sA + KP * NNP, *sR = sB + KP * NX * NUM;
-    double *vq = sR + KP * NUM * NUM, *vp = vq + 64, *wp = vp + 64;
-    const double *any = a.Qinv + onn;  // a valid address for empty ranges
-    const int64_t kb = k0 - 1 + h;     // first block of the A, B, R^-1 ranges
+    double *vq = sm[w], *vp = vq + 64, *wp = vp + 64;
+    double *sQ = wp + 64, *sR = sQ + G::SQ1;  // first phase
+    double *sA = wp + 64, *sB = sA + G::SA;   // second phase
+    const int64_t kb = k0 - 1 + h;     // first block of the ranges
     double rq[regs_for<(KP + 1) * NN>()], ra[regs_for<KP * NN>()], rb[regs_for<KP * NX * NUM>()],
         rr[regs_for<KP * NUM * NUM>()];
-    ld_range<(KP + 1) * NN>(rq, a.Qinv + onn + (int64_t)(k0 - 1 + h) * NN, (nk + 1 - h) * NN, ln);
-    ld_range<KP * NN>(ra, na ? a.A + onn + kb * NN : any, na * NN, ln);
-    ld_range<KP * NX * NUM>(rb, nb ? a.B + it.onu + kb * NX * nu : any, nb, ln);
-    ld_range<KP * NUM * NUM>(rr, nr ? a.Rinv + it.ouu + kb * nu * nu : any, nr, ln);
+    ld_range<(KP + 1) * NN>(rq, a.Qinv + onn + kb * NN, (nk + 1 - h) * NN, ln);
+    ld_range<KP * NUM * NUM>(rr, a.Rinv + it.ouu + kb * nu * nu, nr, ln);
+    ld_range<KP * NN>(ra, a.A + onn + kb * NN, na * NN, ln);
+    ld_range<KP * NX * NUM>(rb, a.B + it.onu + kb * NX * nu, nb, ln);
     // this lane's knot k = k0 + s and row i (clamped for the idle lanes)
     const int s = min(ln / RL, nk - 1), i = min(ln % RL, NX - 1), iu = min(ln % RL, max(nu, 1) - 1);
-    const int k = k0 + s;
+    const int k = k0 + s, sp = max(s - h, 0);
     const bool prev = k > 0, row = ln / RL < nk && ln % RL < NX, urow = ln / RL < nk && ln % RL < nu;
     const double qk = q[ov + (int64_t)k * NX + i];
     const double qp = prev ? q[ov + (int64_t)(k - 1) * NX + i] : 0.0;
     const double rp = prev && nu > 0 ? r[ou + (int64_t)(k - 1) * nu + iu] : 0.0;
     const double ck = c[ov + (int64_t)k * NX + i];
-    st_rows<(KP + 1) * NN, NX, LD>(sQ + h * NNP, rq, (nk + 1 - h) * NN, ln);
-    st_rows<KP * NN, NX, LD>(sA + h * NNP, ra, na * NN, ln);
-    st_range<KP * NX * NUM>(sB + h * NX * nu, rb, nb, ln);
-    st_range<KP * NUM * NUM>(sR + h * nu * nu, rr, nr, ln);
+    st_range<(KP + 1) * NN>(sQ, rq, ln);
+    st_range<KP * NUM * NUM>(sR, rr, ln);
     double *vqs = vq + s * RL, *vps = vp + s * RL, *wps = wp + s * RL;
     if (row) {
         vq[ln] = qk;
@@ -220,14 +228,16 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
     }
     if (urow) wp[ln] = rp;
     wave_sync();
-    const double y = lds_row<NX>(sQ + (s + 1) * NNP, LD, i, vqs);  // (Q_k^-1 q_k)_i
-    const double yp = lds_row<NX>(sQ + s * NNP, LD, i, vps);       // (Q_{k-1}^-1 q_{k-1})_i
-    const double wr = lds_row_n<NUM>(sR + s * nu * nu, nu, iu, wps, nu);  // (R_{k-1}^-1 r_{k-1})_i
-    wave_sync();  // vp, wp are read above before they are overwritten
+    const double y = lds_row<NX>(sQ + (s + 1 - h) * NN, LD, i, vqs);  // (Q_k^-1 q_k)_i
+    const double yp = lds_row<NX>(sQ + sp * NN, LD, i, vps);          // (Q_{k-1}^-1 q_{k-1})_i
+    const double wr = lds_row_n<NUM>(sR + sp * nu * nu, nu, iu, wps, nu);  // (R_{k-1}^-1 r_{k-1})_i
+    wave_sync();  // vp, wp and the first phase's blocks are read above before they are overwritten
     if (row) vp[ln] = prev ? yp : 0.0;
     if (urow) wp[ln] = prev ? wr : 0.0;
+    st_range<KP * NN>(sA, ra, ln);
+    st_range<KP * NX * NUM>(sB, rb, ln);
     wave_sync();
-    const double ga = lds_row<NX>(sA + s * NNP, LD, i, vps) + lds_row_n<NUM>(sB + s * NX * nu, nu, i, wps, nu);
+    const double ga = lds_row<NX>(sA + sp * NN, LD, i, vps) + lds_row_n<NUM>(sB + sp * NX * nu, nu, i, wps, nu);
     if (row) gamma[ov + (int64_t)k * NX + i] = ck - y + (prev ? ga : 0.0);
 }
 
@@ -237,8 +247,8 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_recover_nx(Build
                                                                          const double *r, const double *lam,
                                                                          double *dx, double *du) {
     using G = KktGeo<NX>;
-    constexpr int NN = G::NN, NUM = G::NUM, LD = G::LD, NNP = G::NNP, KP = G::KP, RL = G::RL;
-    __shared__ double sm[G::WAVES][G::PW];
+    constexpr int NN = G::NN, NUM = G::NUM, LD = G::LD, KP = G::KP, RL = G::RL;
+    __shared__ double sm[G::WAVES][G::PX];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln = threadIdx.x & 63;
     const int64_t g = (int64_t)blockIdx.x * G::WAVES + w;
     if (g >= n) return;  // whole wave; the kernel uses no workgroup barrier
@@ -250,35 +260,36 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_recover_nx(Build
     // of the problem has no A, B, R^-1 term
     const int na = min(nk, N - 1 - k0);
     const int nb = nu > 0 ? na * NX * nu : 0, nr = nu > 0 ? na * nu * nu : 0;
-    double *sQ = sm[w], *sA = sQ + KP * NNP, *sB = sA + KP * NNP, *sR = sB + KP * NX * NUM;
-    double *ls = sR + KP * NUM * NUM, *tx = ls + 64, *tu = tx + 64;
-    const double *any = a.Qinv + onn;
+    double *ls = sm[w], *tx = ls + 64, *tu = tx + 64;
+    double *sA = tu + 64, *sB = sA + G::SA;  // first phase
+    double *sQ = tu + 64, *sR = sQ + G::SQ;  // second phase
     double rq[regs_for<KP * NN>()], ra[regs_for<KP * NN>()], rb[regs_for<KP * NX * NUM>()],
         rr[regs_for<KP * NUM * NUM>()];
+    ld_range<KP * NN>(ra, a.A + onn + (int64_t)k0 * NN, na * NN, ln);
+    ld_range<KP * NX * NUM>(rb, a.B + it.onu + (int64_t)k0 * NX * nu, nb, ln);
     ld_range<KP * NN>(rq, a.Qinv + onn + (int64_t)k0 * NN, nk * NN, ln);
-    ld_range<KP * NN>(ra, na ? a.A + onn + (int64_t)k0 * NN : any, na * NN, ln);
-    ld_range<KP * NX * NUM>(rb, nb ? a.B + it.onu + (int64_t)k0 * NX * nu : any, nb, ln);
-    ld_range<KP * NUM * NUM>(rr, nr ? a.Rinv + it.ouu + (int64_t)k0 * nu * nu : any, nr, ln);
+    ld_range<KP * NUM * NUM>(rr, a.Rinv + it.ouu + (int64_t)k0 * nu * nu, nr, ln);
     const int s = min(ln / RL, nk - 1), i = min(ln % RL, NX - 1), iu = min(ln % RL, max(nu, 1) - 1);
     const int k = k0 + s;
     const bool next = k + 1 < N, row = ln / RL < nk && ln % RL < NX, urow = ln / RL < nk && ln % RL < nu;
     const double lnext = next ? lam[ov + (int64_t)(k + 1) * NX + i] : 0.0;
     const double t0 = q[ov + (int64_t)k * NX + i] + lam[ov + (int64_t)k * NX + i];
     const double s0 = next && nu > 0 ? r[ou + (int64_t)k * nu + iu] : 0.0;
-    st_rows<KP * NN, NX, LD>(sQ, rq, nk * NN, ln);
-    st_rows<KP * NN, NX, LD>(sA, ra, na * NN, ln);
-    st_range<KP * NX * NUM>(sB, rb, nb, ln);
-    st_range<KP * NUM * NUM>(sR, rr, nr, ln);
+    st_range<KP * NN>(sA, ra, ln);
+    st_range<KP * NX * NUM>(sB, rb, ln);
     double *lss = ls + s * RL, *txs = tx + s * RL, *tus = tu + s * RL;
     if (row) ls[ln] = lnext;
     wave_sync();
     // t = q_k + lambda_k - A_k^T lambda_{k+1};  s = r_k - B_k^T lambda_{k+1}
-    const double ta = lds_col<NX>(sA + s * NNP, LD, i, lss);
+    const double ta = lds_col<NX>(sA + s * NN, LD, i, lss);
     const double sb = lds_col<NX>(sB + s * NX * nu, nu, iu, lss);
+    wave_sync();  // the first phase's blocks are read above before they are overwritten
     if (row) tx[ln] = next ? t0 - ta : t0;
     if (urow) tu[ln] = next ? s0 - sb : 0.0;
+    st_range<KP * NN>(sQ, rq, ln);
+    st_range<KP * NUM * NUM>(sR, rr, ln);
     wave_sync();
-    const double dxi = lds_row<NX>(sQ + s * NNP, LD, i, txs);
+    const double dxi = lds_row<NX>(sQ + s * NN, LD, i, txs);
     const double dui = lds_row_n<NUM>(sR + s * nu * nu, nu, iu, tus, nu);
     if (row) dx[ov + (int64_t)k * NX + i] = dxi;
     if (urow) du[ou + (int64_t)k * nu + iu] = next ? dui : 0.0;

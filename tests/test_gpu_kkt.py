@@ -176,3 +176,29 @@ def test_build_without_stored_inverses(kind, prec):
         sv, su = slice(b.off_v[i], b.off_v[i + 1]), slice(off_u[i], off_u[i + 1])
         _, g_ref = oracle.kkt_rhs(p["A"], p["B"], p["Q"], p["R"], q[sv], r[su], c[sv])
         assert np.abs(g[sv] - g_ref).max() <= 1e-10 * np.abs(g_ref).max(), i
+
+
+@pytest.mark.parametrize("nx,nu", [(6, 3), (6, 1), (6, 0), (14, 7), (14, 2), (14, 0), (26, 13), (26, 5), (26, 0)])
+def test_kkt_calls_at_the_edges_of_a_wave(nx, nu):
+    """Horizons around the knots a wave takes (8, 4 and 1), full, partial and no controls; tolerance as above."""
+    from paper_2309_06427_amd import solver
+    rng = np.random.default_rng(100 * nx + nu)
+    b = inputs.pack([inputs.draw_problem(rng, N, nx, nu) for N in (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17)])
+    q, r, c, off_u = vectors(b, nx + nu)
+    lam = np.random.default_rng(nu).standard_normal(int(b.off_v[-1]))
+    with solver.DeviceBatch(b) as db:
+        db.build("sym", "fp64")
+        db.kkt_rhs(dev(q), dev(r), dev(c))
+        db.lam.copy_(dev(lam))
+        dx, du = db.kkt_recover(dev(q), dev(r))
+        torch.cuda.synchronize()
+        g, dx, du = db.gamma.cpu().numpy(), dx.cpu().numpy(), du.cpu().numpy()
+    for i in range(b.P):
+        p = b.problem(i)
+        sv, su = slice(b.off_v[i], b.off_v[i + 1]), slice(off_u[i], off_u[i + 1])
+        _, g_ref = oracle.kkt_rhs(p["A"], p["B"], p["Q"], p["R"], q[sv], r[su], c[sv])
+        assert np.abs(g[sv] - g_ref).max() <= 1e-10 * np.abs(g_ref).max(), i
+        _, dx_ref, du_ref = oracle.kkt_recover(p["A"], p["B"], p["Q"], p["R"], q[sv], r[su], lam[sv])
+        assert np.abs(dx[sv] - dx_ref).max() <= 1e-10 * np.abs(dx_ref).max(), i
+        if nu:
+            assert np.abs(du[su] - du_ref).max() <= 1e-10 * max(np.abs(du_ref).max(), 1e-300), i
