@@ -237,7 +237,9 @@ hipError_t gemm(int M, int N, int K, int splits, const AL &al, const BL &bl, con
 // by up to 128 hidden units per workgroup (MT = 64: 4 waves, each 16 knots x
 // 128 units as 8 MFMA tiles; MT = 16, for few knots: each wave 16 knots x 32
 // units), K in steps of 32 through two LDS buffers.  A
-// thread gathers MT / 8 consecutive raw inputs of one knot per step through a
+// row's threads gather its raw inputs in turn (a load's lanes on few cache
+// lines: these gathers, not the products, bound the kernel), gamma only in
+// the last steps, which hold it, through a
 // table of input offsets built in LDS at the start (D_k from its packed upper
 // triangle, L_k, gamma_k); the step's 32 means and inverse deviations go to
 // LDS beside the tile and standardise each A operand as it is read (features
@@ -247,7 +249,8 @@ hipError_t gemm(int M, int N, int K, int splits, const AL &al, const BL &bl, con
 // so that no wait separates them.
 constexpr int kL1N = 128, kL1K = 32;
 // Knots up to which MT is 16: 64-knot workgroups give 8192 knots 128 of 256 CUs.  Measured with either, one nx 26
-// inference: 2048 knots 167 (MT = 64) and 87 us (16), 8192 knots 190 and 131, 12288 knots 190 and 201.
+// inference: 2048 knots 167 (MT = 64) and 87 us (16), 8192 knots 190 and 131, 12288 knots 190 and 201; with a row's
+// inputs dealt out in turn 4608 knots 86 us (16), 9216 knots 140 (64), and 57600 knots 479 where they took 659.
 constexpr int kL1Few = 8192;
 constexpr int kFeatL = 1, kFeatG = 2;  // input kinds in the table's top bits (0: D_k)
 constexpr int kL1MaxIn = 3136;         // table entries (the static tiles leave room for these)
@@ -278,7 +281,8 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
         foff[f] = v;
     }
     // this thread's A row and its inputs of each step
-    const int am = t / (kL1K / EA), aq = (t % (kL1K / EA)) * EA;
+    constexpr int TR = kL1K / EA;  // threads per row, which take its inputs in turn: a row's loads share cache lines
+    const int am = t / TR, aq = t % TR;
     const KnotInfo q = s.ki[min(m0 + am, s.M - 1)];  // rows past M: a valid knot (outputs not stored)
     const TM *src = (const TM *)s.B3 + q.blk;
     const double *gsrc = s.gamma + q.vec;
@@ -302,12 +306,19 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
     auto load = [&](int k0) {
 #pragma unroll
         for (int j = 0; j < EA; ++j) {
-            const int fc = min(k0 + aq + j, nlast);
+            const int fc = min(k0 + aq + TR * j, nlast);
             const int e = foff[fc], kind = (int)((unsigned)e >> 30), o = e & 0x3fffffff;
             rd[j] = src[kind == kFeatG ? 0 : o];
-            rg[j] = gsrc[kind == kFeatG ? o : 0];
             wd[j] = (kind == kFeatG || (kind == kFeatL && q.first)) ? 0.f : 1.f;
             wg[j] = kind == kFeatG ? 1.f : 0.f;
+            rg[j] = 0.0;
+        }
+        if (k0 + kL1K > 2 * nn) {  // only the last steps hold parts of gamma
+#pragma unroll
+            for (int j = 0; j < EA; ++j) {
+                const int e = foff[min(k0 + aq + TR * j, nlast)];
+                rg[j] = gsrc[(int)((unsigned)e >> 30) == kFeatG ? e & 0x3fffffff : 0];
+            }
         }
         const int kr = k0 + bk;
         const float *wrow = W1 + (int64_t)min(kr, nlast) * H;
@@ -325,7 +336,7 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
     load(0);
     for (int k0 = 0, buf = 0; k0 < nin; k0 += kL1K, buf ^= 1) {
 #pragma unroll
-        for (int j = 0; j < EA; ++j) As[buf][aq + j][am] = (float)rd[j] * wd[j] + (float)rg[j] * wg[j];
+        for (int j = 0; j < EA; ++j) As[buf][aq + TR * j][am] = (float)rd[j] * wd[j] + (float)rg[j] * wg[j];
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
