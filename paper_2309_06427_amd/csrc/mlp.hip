@@ -22,6 +22,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int T = 32, BK = 32, GT = 256, PADL = 4;
+constexpr int kWideIn = 256;     // inputs from which their weight gradient takes 64 columns per tile
 constexpr int kSplitStep = 16;  // K ranges are multiples of this
 
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
@@ -140,22 +141,24 @@ struct EpGeluBack {  // dZ = v * gelu'(Z)
 
 // ------------------------------------------------------------------- GEMM ---
 // C = op(A) op(B) over k in [z * kspl, min(K, (z + 1) * kspl)), z = blockIdx.z,
-// for a T x T tile of C per workgroup, each wave a 16 x 16 quarter of it.
+// for a T x TN tile of C per workgroup, each wave a 16 x TN / 2 quarter of it.
 // Bound by the latency of its loads (short K ranges, operands gathered an
 // element at a time): 32 x 32 tiles, 8 workgroups per CU, beat 64 x 64 ones at
 // every size from 2304 to 57600 knots (a step's loss and gradient, nx 14, 2304
 // knots: 180 us with 64 x 64 tiles, 131 us; nx 26, 57600 knots: 3.95 and 3.66
 // ms).
-template <class AL, class BL, class EP>
+template <int TN, class AL, class BL, class EP>
 __global__ __launch_bounds__(GT) void k_gemm(int M, int N, int K, int kspl, AL al, BL bl, EP ep) {
     __shared__ float As[2][BK][T + PADL];
-    __shared__ float Bs[2][BK][T + PADL];
-    constexpr int EA = T * BK / GT, EB = EA;  // elements per thread and operand
+    __shared__ float Bs[2][BK][TN + PADL];
+    constexpr int EA = T * BK / GT, EB = TN * BK / GT, NT = TN / 32;  // elements per thread, MFMA tiles per wave
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int m0 = blockIdx.x * T, n0 = blockIdx.y * T, z = blockIdx.z;
-    const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (T / 2);
+    const int m0 = blockIdx.x * T, n0 = blockIdx.y * TN, z = blockIdx.z;
+    const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (TN / 2);
     const int kb = z * kspl, ke = min(K, kb + kspl);
-    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     // this thread's element e of a tile
     auto at_a = [&](int e, int &mm, int &kk) {
         const int idx = t + GT * e;
@@ -164,8 +167,8 @@ __global__ __launch_bounds__(GT) void k_gemm(int M, int N, int K, int kspl, AL a
     };
     auto at_b = [&](int e, int &nn, int &kk) {
         const int idx = t + GT * e;
-        nn = BL::kFast ? idx / BK : idx % T;
-        kk = BL::kFast ? idx % BK : idx / T;
+        nn = BL::kFast ? idx / BK : idx % TN;
+        kk = BL::kFast ? idx % BK : idx / TN;
     };
     // the next tile's elements are fetched before this tile's products and go to the other LDS buffer, one barrier a
     // step: the short K ranges of a training step's products are bound by this latency
@@ -203,15 +206,20 @@ __global__ __launch_bounds__(GT) void k_gemm(int M, int N, int K, int kspl, AL a
 #pragma unroll
         for (int sub = 0; sub < BK / 4; ++sub) {
             const int kr = 4 * sub + (lane >> 4), c = lane & 15;
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(As[buf][kr][wm + c], Bs[buf][kr][wn + c], acc, 0, 0, 0);
+            const float a = As[buf][kr][wm + c];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[buf][kr][wn + 16 * j + c], acc[j], 0, 0, 0);
         }
     }
-    // lane l holds rows 4 (l / 16) + r, column l % 16 of its wave's tile
+    // lane l holds rows 4 (l / 16) + r, column l % 16 of each 16 x 16 tile
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 4 * (lane >> 4) + r, n = n0 + wn + (lane & 15);
-        if (m < M && n < N) ep(m, n, z, acc[r]);
-    }
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + wm + 4 * (lane >> 4) + r, n = n0 + wn + 16 * j + (lane & 15);
+            if (m < M && n < N) ep(m, n, z, acc[j][r]);
+        }
 }
 
 // K range of each of about `splits` parts, and their number
@@ -224,11 +232,11 @@ int split_count(int K, int splits) {
     return K > 0 ? (K + kspl - 1) / kspl : 1;
 }
 
-template <class AL, class BL, class EP>
+template <int TN = 32, class AL, class BL, class EP>
 hipError_t gemm(int M, int N, int K, int splits, const AL &al, const BL &bl, const EP &ep, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
     const int nz = split_count(K, splits), kspl = split_length(K, splits);
-    hipLaunchKernelGGL((k_gemm<AL, BL, EP>), dim3((M + T - 1) / T, (N + T - 1) / T, nz), dim3(GT), 0, s, M, N, K,
+    hipLaunchKernelGGL((k_gemm<TN, AL, BL, EP>), dim3((M + T - 1) / T, (N + TN - 1) / TN, nz), dim3(GT), 0, s, M, N, K,
                        kspl, al, bl, ep);
     return hipGetLastError();
 }
@@ -261,7 +269,7 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
                                                int H, float *__restrict__ Z, float *__restrict__ Hout) {
     constexpr int EA = MT / 8, NT = MT / 8;  // inputs per thread and step, tiles per wave
     __shared__ float As[2][kL1K][MT + PADL];
-    __shared__ float Bs[2][kL1K][kL1N + PADL];
+    __shared__ __align__(16) float Bs[2][kL1K][kL1N + PADL];
     __shared__ float Ms[2][2][kL1K];  // mean, inverse deviation of the step's inputs
     __shared__ int foff[kL1MaxIn];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -286,10 +294,10 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
     const KnotInfo q = s.ki[min(m0 + am, s.M - 1)];  // rows past M: a valid knot (outputs not stored)
     const TM *src = (const TM *)s.B3 + q.blk;
     const double *gsrc = s.gamma + q.vec;
-    // B tile: row t / 8 of the step, sixteen columns from 16 (t % 8); the
+    // B tile: row t / 8 of the step, columns 4 (t % 8) + 32 c .. + 3; the
     // first 64 threads also fetch the step's scaling (t < 32 means, else
     // inverse deviations)
-    const int bk = t >> 3, bn = (t & 7) * 16;
+    const int bk = t >> 3, bn = (t & 7) * 4;
     const int nlast = nin - 1;
     f32x4 acc[NT];
 #pragma unroll
@@ -324,7 +332,7 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
         const float *wrow = W1 + (int64_t)min(kr, nlast) * H;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int n = n0 + bn + 4 * c;
+            const int n = n0 + bn + 32 * c;
             rb[c] = *(const f32x4 *)(wrow + min(n, H - 4));
             wb[c] = (kr < nin && n < H) ? 1.f : 0.f;
         }
@@ -338,9 +346,7 @@ __global__ __launch_bounds__(GT) void k_layer1(FeatSrc s, const float *__restric
 #pragma unroll
         for (int j = 0; j < EA; ++j) As[buf][aq + TR * j][am] = (float)rd[j] * wd[j] + (float)rg[j] * wg[j];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Bs[buf][bk][bn + 4 * c + r] = rb[c][r] * wb[c];
+        for (int c = 0; c < 4; ++c) *(f32x4 *)&Bs[buf][bk][bn + 32 * c] = rb[c] * wb[c];
         if (t < 64) Ms[buf][t >> 5][t & 31] = rs * ws;
         __syncthreads();  // this buffer is full; the other one's readers are done (they passed this barrier)
         load(k0 + kL1K);  // past nin: clamped addresses, zero scaling
@@ -646,7 +652,13 @@ hipError_t backward_t(const FeatSrc &f, const NetView &w, const float *mu, const
     if ((e = gemm(M, H, H, 1, RowA{dZ2, H, M, H}, ColB{w.W2, H, H, H}, EpGeluBack{Z1, dZ1, H}, s))) return e;
     // layer 1 (inputs re-read from the stored blocks)
     FeatAT<TM> ft{FeatA<TM>{f, mu, isd, nin}};
-    if ((e = gemm(nin, H, M, kSplits, ft, RowB{dZ1, H, M, H}, part(0, H), s))) return e;
+    // 64 columns per tile gather each input half as often; with few inputs (nx 6: 78) that leaves too few workgroups.
+    // A step's loss and gradient, 32 and 64 columns, 18432 knots: nx 6 394 and 409 us, nx 14 547 and 536, nx 26 1057
+    // and 956.
+    const EpStore p0 = part(0, H);
+    const RowB z1{dZ1, H, M, H};
+    if ((e = nin >= kWideIn ? gemm<64>(nin, H, M, kSplits, ft, z1, p0, s) : gemm(nin, H, M, kSplits, ft, z1, p0, s)))
+        return e;
     hipLaunchKernelGGL(k_grad_end, dim3(end.sums + grid_for(end.cnt[0] + end.cnt[1] + end.cnt[2], 256)), dim3(256),
                        0, s, end);
     return hipGetLastError();
