@@ -136,13 +136,14 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
 // FP64 without a chosen mapping: one workgroup of 512 threads per CU, whose step holds 6 to 80 knots of a problem,
 // where 128 threads hold one knot of 26 states, half a wave's work between two barriers.  Only where a small state
 // size leaves several small workgroups per CU with problems of their own are 256 threads better.  Measured, 128 /
-// 256 / 512 threads in ms: nx 26 x 1024 problems (106 iterations) 113 / 61 / 37, x 16 13.6 / 7.1 / 2.4; nx 20 x 512
-// 15.8 / 8.4 / 4.0; nx 14 x 1024 3.55 / 2.84 / 3.32, x 16 2.36 / 1.37 / 0.80; nx 9 x 512 1.81 / 1.02 / 1.02; nx 6 x
-// 1024 0.85 / 0.80 / 1.04, x 16 0.62 / 0.42 / 0.29.
+// 256 / 512 threads in ms: nx 26 x 1024 problems of condition 1e6 156 / 120 / 53, x 16 16.4 / 8.1 / 2.4; nx 20 x 512
+// 14.6 / 7.8 / 3.9; nx 14 x 1024 3.77 / 3.07 / 2.71, x 2500 - / 7.32 / 6.63, x 16 2.67 / 1.49 / 0.75; nx 13 x 1024
+// - / 4.28 / 4.05; nx 12 x 1024 - / 3.28 / 3.24, x 600 - / 2.00 / 2.16; nx 10 x 1024 - / 2.22 / 2.48; nx 9 x 512
+// 1.75 / 0.98 / 1.05; nx 6 x 1024 0.90 / 0.90 / 1.14, x 16 0.69 / 0.45 / 0.31.
 void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, int *lds) {
     const bool chosen = g.threads > 0 || b->mapping_set;
     int t = g.threads > 0 ? g.threads : b->threads;
-    if (!chosen && !b->fp32) t = g.nx < 16 && g.count > 2 * b->cus ? 256 : 512;
+    if (!chosen && !b->fp32) t = g.nx < 13 && g.count > 2 * b->cus ? 256 : 512;
     *threads = t;
     *lds = 0;
     if (!ssp::pcg2_threads_ok(t) && (chosen || t != 512)) return;

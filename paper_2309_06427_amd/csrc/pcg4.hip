@@ -16,6 +16,12 @@
 // time.  (Oh v)_k = a_k + c_{k+1}; c crosses from lane group g + 1 to g by a shuffle, and from a wave's first set to
 // the wave before it through LDS, completed after the barrier that ends a product.
 //
+// What bounds it: issue of the products' multiply-adds (a wave issues one every 8 cycles or so, and registers leave two
+// waves per SIMD) and, at 26, the LDS transposition: 28 of 38 thousand cycles of a pass over 144 knots, updates, inner
+// products and scalars share the rest; more sets in registers at 26 spill, and a second column-wise copy there gains
+// nothing.  Measured, streaming and on chip, 1365 problems of 144 knots: nx 26 5.37 and 3.07 ms, nx 14 1.83 and 1.01
+// ms; 16 problems of up to 256 knots 3.6 and 1.2 ms with their build.
+//
 // Rounding: the float arithmetic is that of the streaming solve, term by term.  A row's product sums its even and
 // odd terms apart; the inner products are accumulated per lane in the order of the streaming solve's pipeline
 // steps and summed by the same trees (dots4), so both solves return the same bits.
