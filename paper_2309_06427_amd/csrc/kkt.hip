@@ -97,8 +97,11 @@ struct KktGeo {
     // TB/s; the right-hand side reads each Q^-1 twice, mostly from L2).
     static constexpr int SA = ranges(KP * NN), SB = ranges(KP * NX * NUM), SR = ranges(KP * NUM * NUM);
     static constexpr int SQ1 = ranges((KP + 1) * NN), SQ = ranges(KP * NN);
-    static constexpr int PR = (SQ1 + SR > SA + SB ? SQ1 + SR : SA + SB) + 3 * 64;
-    static constexpr int PX = (SQ + SR > SA + SB ? SQ + SR : SA + SB) + 3 * 64;
+    // At nx 6 all blocks are in LDS at once: 16 waves per CU fit so, and one phase is the shorter chain (4000 problems:
+    // recovery 103.0 us in one phase, 103.8 in two; 30 problems of mixed sizes 12.4 and 13.5).
+    static constexpr bool ONE = KP == 8;
+    static constexpr int PR = (ONE ? SQ1 + SR + SA + SB : SQ1 + SR > SA + SB ? SQ1 + SR : SA + SB) + 3 * 64;
+    static constexpr int PX = (ONE ? SQ + SR + SA + SB : SQ + SR > SA + SB ? SQ + SR : SA + SB) + 3 * 64;
     static constexpr int WAVES = KP == 8 ? 4 : 1;  // waves per workgroup
 };
 
@@ -203,7 +206,7 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
     const int nb = nu > 0 ? na * NX * nu : 0, nr = nu > 0 ? na * nu * nu : 0;
     double *vq = sm[w], *vp = vq + 64, *wp = vp + 64;
     double *sQ = wp + 64, *sR = sQ + G::SQ1;  // first phase
-    double *sA = wp + 64, *sB = sA + G::SA;   // second phase
+    double *sA = G::ONE ? sR + G::SR : wp + 64, *sB = sA + G::SA;  // second phase
     const int64_t kb = k0 - 1 + h;     // first block of the ranges
     double rq[regs_for<(KP + 1) * NN>()], ra[regs_for<KP * NN>()], rb[regs_for<KP * NX * NUM>()],
         rr[regs_for<KP * NUM * NUM>()];
@@ -221,6 +224,11 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
     const double ck = c[ov + (int64_t)k * NX + i];
     st_range<(KP + 1) * NN>(sQ, rq, ln);
     st_range<KP * NUM * NUM>(sR, rr, ln);
+    auto second = [&]() {
+        st_range<KP * NN>(sA, ra, ln);
+        st_range<KP * NX * NUM>(sB, rb, ln);
+    };
+    if constexpr (G::ONE) second();
     double *vqs = vq + s * RL, *vps = vp + s * RL, *wps = wp + s * RL;
     if (row) {
         vq[ln] = qk;
@@ -234,8 +242,7 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_rhs_nx(BuildArgs
     wave_sync();  // vp, wp and the first phase's blocks are read above before they are overwritten
     if (row) vp[ln] = prev ? yp : 0.0;
     if (urow) wp[ln] = prev ? wr : 0.0;
-    st_range<KP * NN>(sA, ra, ln);
-    st_range<KP * NX * NUM>(sB, rb, ln);
+    if constexpr (!G::ONE) second();
     wave_sync();
     const double ga = lds_row<NX>(sA + sp * NN, LD, i, vps) + lds_row_n<NUM>(sB + sp * NX * nu, nu, i, wps, nu);
     if (row) gamma[ov + (int64_t)k * NX + i] = ck - y + (prev ? ga : 0.0);
@@ -262,7 +269,7 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_recover_nx(Build
     const int nb = nu > 0 ? na * NX * nu : 0, nr = nu > 0 ? na * nu * nu : 0;
     double *ls = sm[w], *tx = ls + 64, *tu = tx + 64;
     double *sA = tu + 64, *sB = sA + G::SA;  // first phase
-    double *sQ = tu + 64, *sR = sQ + G::SQ;  // second phase
+    double *sQ = G::ONE ? sB + G::SB : tu + 64, *sR = sQ + G::SQ;  // second phase
     double rq[regs_for<KP * NN>()], ra[regs_for<KP * NN>()], rb[regs_for<KP * NX * NUM>()],
         rr[regs_for<KP * NUM * NUM>()];
     ld_range<KP * NN>(ra, a.A + onn + (int64_t)k0 * NN, na * NN, ln);
@@ -277,6 +284,11 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_recover_nx(Build
     const double s0 = next && nu > 0 ? r[ou + (int64_t)k * nu + iu] : 0.0;
     st_range<KP * NN>(sA, ra, ln);
     st_range<KP * NX * NUM>(sB, rb, ln);
+    auto second = [&]() {
+        st_range<KP * NN>(sQ, rq, ln);
+        st_range<KP * NUM * NUM>(sR, rr, ln);
+    };
+    if constexpr (G::ONE) second();
     double *lss = ls + s * RL, *txs = tx + s * RL, *tus = tu + s * RL;
     if (row) ls[ln] = lnext;
     wave_sync();
@@ -286,8 +298,7 @@ __global__ __launch_bounds__(64 * KktGeo<NX>::WAVES) void k_kkt_recover_nx(Build
     wave_sync();  // the first phase's blocks are read above before they are overwritten
     if (row) tx[ln] = next ? t0 - ta : t0;
     if (urow) tu[ln] = next ? s0 - sb : 0.0;
-    st_range<KP * NN>(sQ, rq, ln);
-    st_range<KP * NUM * NUM>(sR, rr, ln);
+    if constexpr (!G::ONE) second();
     wave_sync();
     const double dxi = lds_row<NX>(sQ + s * NN, LD, i, txs);
     const double dui = lds_row_n<NUM>(sR + s * nu * nu, nu, iu, tus, nu);
