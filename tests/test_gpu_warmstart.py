@@ -289,3 +289,15 @@ def test_prediction_is_the_same_in_small_and_large_batches(nx, H, P):
     df.build("sym", "fp32_refine64")
     net, _ = _net(nx, H, 8)
     assert torch.equal(net.predict(db)[-3 * 64 * nx:], net.predict(df))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32_refine64"])
+def test_loss_and_gradient_at_26_states(prec):
+    """The residual kernels compiled for 26 states, one knot to several workgroups of rows."""
+    b, db, probs, lam_star = _pool(26, 4, 21, N_range=(1, 25), prec=prec)
+    net, theta = _net(26, 32, 9)
+    loss = net.loss_grad(db, 0, 4, lam_star)
+    mu, isd, ys = net.get_scaling()
+    ref_loss, ref_g = mlp.loss_and_grad(theta, probs, mu.astype(np.float64), isd.astype(np.float64), ys, 26, 32)
+    assert abs(float(loss) - ref_loss) <= 2e-4 * ref_loss
+    assert rel(net.get_grad(), ref_g) < 2e-4
