@@ -151,7 +151,7 @@ void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, 
     if (need == 0) return;
     int l = g.lds > 0 ? g.lds : (b->lds_bytes > 0 ? b->lds_bytes : need);
     l = std::max(l, ssp::bt_sweep_min_lds(g.nx, true, 8));
-    if (l > ssp::kFusedLdsCap) return;
+    if (l > ssp::pcg2_lds_cap(b->fp32, t)) return;
     if (ssp::pcg2_steps_for(g.nx, b->fp32, t, l) < 1) return;
     *lds = l;
 }

@@ -587,9 +587,14 @@ int pcg2_steps_for(int nx, bool fp32, int threads, int lds_bytes) {
                 : pcg2_knots_per_step<double>(nx, threads, lds_bytes);
 }
 
+int pcg2_lds_cap(bool fp32, int threads) {
+    const int waves = threads / kWave, cap = 160 * 1024 - waves * (2 * 8 + 3 * (fp32 ? 4 : 8));
+    return cap < kFusedLdsCap ? cap : kFusedLdsCap;
+}
+
 int pcg2_lds(int nx_max, bool fp32, int threads) {
     // ring budget for C knots of the largest nx, at least the FP64 residual sweep
-    const int eb = fp32 ? 4 : 8;
+    const int eb = fp32 ? 4 : 8, cap = pcg2_lds_cap(fp32, threads);
     int C = fp32 ? pcg2_knots_per_step<float>(nx_max, threads, 1 << 30)
                  : pcg2_knots_per_step<double>(nx_max, threads, 1 << 30);
     if (C < 1) return 0;
@@ -599,10 +604,10 @@ int pcg2_lds(int nx_max, bool fp32, int threads) {
     int bytes = (C + 2) * per + nxp * eb + 16;
     const int res = bt_sweep_min_lds(nx_max, true, 8);
     if (bytes < res) bytes = res;
-    if (bytes > kFusedLdsCap) {
+    if (bytes > cap) {
         // shrink the step to the LDS limit
-        C = (kFusedLdsCap - nxp * eb - 16) / per - 2;
-        if (C < 1 || res > kFusedLdsCap) return 0;
+        C = (cap - nxp * eb - 16) / per - 2;
+        if (C < 1 || res > cap) return 0;
         bytes = (C + 2) * per + nxp * eb + 16;
         if (bytes < res) bytes = res;
     }
