@@ -1071,6 +1071,7 @@ const void *pcg4_kernel(int nx) {
 
 template <int NX>
 static int64_t need4(int N, int nvec) {
+    if (N > 1 << 20) return INT64_MAX;  // far past any LDS, and vec4_floats overflows further on
     const int64_t v = lds4_bytes<NX>(N, nvec);
     constexpr int o = waves4<NX>() * wave_bytes4<NX>();
     return v > o ? v : o;
