@@ -406,6 +406,17 @@ ssp_status ssp_get_scaled_mapping(const ssp_batch *b, int32_t *threads, int32_t 
 ssp_status ssp_scaled_onchip_horizon(int32_t nx, ssp_precon pc, ssp_precision prec, int32_t threads,
                                      int32_t lds_bytes, int32_t *max_n);
 
+/* How many problems of state size nx the next ssp_solve of the current build
+ * holds on chip: in the scaled solve under FP32 storage, with the default
+ * mapping and FP32 sums (ssp_set_reduction_fp64 off), a problem of state size
+ * 6, 14 or 26 whose vectors fit a CU's LDS can run with its Oh blocks in
+ * registers and L2 and its vectors in LDS instead of streaming them each pass.
+ * They are the shortest *count problems of that state size; the others
+ * stream.  Both forms return the same bits.  0 under any other solve;
+ * SSP_ERR_ARG for a null count or a state size that the batch does not have,
+ * SSP_ERR_STATE before the first build. */
+ssp_status ssp_scaled_onchip_problems(const ssp_batch *b, int32_t nx, int32_t *count);
+
 /* The kernel the last ssp_solve (or ssp_autotune) of this batch enqueued:
  * 1 explicit two-sweep, 2 fused (one workgroup per problem), 3 cooperative
  * (one problem over the whole grid), 4 scaled (a persistent grid per state

@@ -59,6 +59,7 @@ SIGNATURES = {
     "ssp_get_mapping": (C.c_int, [_vp, _i32, _pi32, _pi32, _pi32, C.POINTER(_f), _pi32]),
     "ssp_solve_kernel": (C.c_int, [_vp, _pi32, _pi32, _pi32]),
     "ssp_set_scaled_mapping": (C.c_int, [_vp, _i32, _i32]),
+    "ssp_scaled_onchip_problems": (C.c_int, [_vp, _i32, _pi32]),
     "ssp_get_scaled_mapping": (C.c_int, [_vp, _pi32, _pi32, _pi32, C.POINTER(_f)]),
     "ssp_copy_bytes": (C.c_int, [_vp, _vp, _i64, _vp]),
     "ssp_status_str": (C.c_char_p, [C.c_int]),

@@ -100,6 +100,15 @@ bool scaled_fits(const ssp_batch *b, int threads, int lds, int m) {
     return true;
 }
 
+// Problems of a group that the scaled solve of the current build holds on chip: the last ones of the group's order.  The
+// problems that fit a CU's registers and LDS run there when the mapping is the default one (the on-chip solve repeats
+// that mapping's sums, and returns the same bits); any other mapping, and the longer ones, stream.
+int chip_count(const ssp_batch *b, const ssp_batch::Group &g) {
+    const int t = b->s3_threads, m = poly_steps(b->pc), lds = scaled_lds(b, t, m);
+    if (!b->scaled || !b->fp32 || b->acc64 || t != 256 || lds != scaled_lds_default(b, t, m)) return 0;
+    return ssp::pcg3_steps_for(g.nx, b->fp32, t, lds, m) > m + 1 ? g.count - g.streamed : 0;
+}
+
 ssp_status alloc_storage(ssp_batch *b, bool fp32) {
     if (b->have_storage && b->fp32 == fp32) return SSP_OK;
     free_storage(b);
@@ -304,10 +313,6 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
     // preconditioned S, so the first inner solve may aim at theta tol itself
     // (no floor above it): one outer step then suffices for most problems
     a.tau_min = b->prec == SSP_FP64 ? 1e-15 : std::min(1e-6, a.theta * a.tol);
-    // The problems that fit a CU's registers and LDS run the on-chip solve when the mapping is the default one (it
-    // repeats that mapping's sums, and returns the same bits); the longer ones, which come first in their group's
-    // order, and any other mapping stream.
-    const bool chip = b->fp32 && !a.acc64 && t == 256 && a.lds_bytes == scaled_lds_default(b, t, a.poly);
     // one persistent grid per state size (largest total work first), each
     // with its own queue counter, on internal streams forked from and joined
     // back into s: a grid whose queue is empty retires and the next size's
@@ -326,7 +331,7 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
         ga.queue = a.queue + 2 * i;
         ga.step_knots = ssp::pcg3_steps_for(g.nx, b->fp32, t, a.lds_bytes, a.poly);
         ga.res_knots = ssp::pcg3_residual_steps(g.nx, b->fp32, a.lds_bytes);
-        const int streamed = chip && ga.step_knots > a.poly + 1 ? g.streamed : g.count;
+        const int streamed = g.count - chip_count(b, g);
         ga.nprob = streamed;
         SSP_HIP(ssp::launch_pcg3(ga, b->fp32, t, g.nx, 0, fork ? b->gstreams[i] : s));
         ga.order += streamed;
@@ -1211,6 +1216,17 @@ ssp_status ssp_get_scaled_mapping(const ssp_batch *b, int32_t *threads, int32_t 
         *grid = std::min(occ * cus, b->P);
     }
     return SSP_OK;
+}
+
+ssp_status ssp_scaled_onchip_problems(const ssp_batch *b, int32_t nx, int32_t *count) {
+    if (!b || !count) return SSP_ERR_ARG;
+    for (const auto &g : b->groups) {
+        if (g.nx != nx) continue;
+        if (!b->built) return SSP_ERR_STATE;
+        *count = chip_count(b, g);
+        return SSP_OK;
+    }
+    return SSP_ERR_ARG;
 }
 
 ssp_status ssp_solve_kernel(const ssp_batch *b, int32_t *kernel, int32_t *W, int32_t *G) {

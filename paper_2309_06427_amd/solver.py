@@ -139,6 +139,12 @@ class BatchSolver:
               "ssp_get_scaled_mapping")
         return int(t.value), int(l.value), int(g.value), float(ms.value)
 
+    def onchip_problems(self, nx: int) -> int:
+        """How many problems of state size nx (its shortest ones) the next solve of this build holds on chip."""
+        n = C.c_int32()
+        check(_lib.load().ssp_scaled_onchip_problems(self._h, int(nx), C.byref(n)), "ssp_scaled_onchip_problems")
+        return int(n.value)
+
     def solve_kernel(self) -> tuple:
         """(kernel, W, G) of the last solve: 1 explicit, 2 fused, 3 cooperative,
         4 scaled (W own knots per workgroup, G workgroups of the cooperative
