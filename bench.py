@@ -110,19 +110,16 @@ def onchip_mask(b, pc: str, precision: str, mapping) -> np.ndarray:
     return np.array([int(b.N[i]) <= hor[int(b.nx[i])] for i in range(b.P)], dtype=bool)
 
 
-def chip_mask(b, precision: str, default_mapping: bool) -> np.ndarray:
-    """Problems the scaled solve holds on chip (the library's rule): FP32
-    storage, the default mapping, horizons whose vectors fit a CU's LDS, and
-    at nx 6 no more problems than the CUs take in a few rounds."""
-    import torch
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    limit = {6: 2128, 14: 768, 26: 360}
-    ok = np.array([precision != "fp64" and default_mapping and int(b.N[i]) <= limit.get(int(b.nx[i]), 0)
-                   for i in range(b.P)], dtype=bool)
-    small = ok & (b.nx == 6)
-    if small.any() and small.sum() > (2.5 if b.N[small].max() <= 256 else 1.0) * cus:
-        ok &= ~small
-    return ok
+def chip_mask(b, solver) -> np.ndarray:
+    """Problems that the next solve of the handle holds on chip: the library
+    says how many of each state size, and they are its shortest ones (ties:
+    the later ones)."""
+    on = np.zeros(b.P, dtype=bool)
+    for x in np.unique(b.nx):
+        ids = np.nonzero(b.nx == x)[0]
+        order = ids[np.argsort(-b.N[ids].astype(np.int64), kind="stable")]
+        on[order[len(order) - solver.onchip_problems(int(x)):]] = True
+    return on
 
 
 def scaled_bytes(b, iters, outer, precision: str, onchip=None, chip=None):
@@ -338,7 +335,6 @@ def main() -> int:
     stream = torch.cuda.current_stream()
     mapping = None
     db.build(args.pc, precision)
-    default_mapping = db.solver.scaled_mapping()[:2]
     if args.mapping:
         # a fixed per-state-size mapping, "nx:threads:lds,..." (e.g. from an earlier autotune)
         for item in args.mapping.split(","):
@@ -439,10 +435,8 @@ def main() -> int:
     if args.graph:
         ok = ok and all(r["graph_matches_eager"] for r in runs.values())
     kern, coop_w, coop_g = db.solver.solve_kernel()  # the kernel the solves ran: 1 explicit, 2 fused, 3 cooperative
-    sm = db.solver.scaled_mapping()
-    is_default = sm[:2] == default_mapping
-    oc = onchip_mask(b, args.pc, precision, sm) if kern == 4 else None
-    ch = chip_mask(b, precision, is_default) if kern == 4 else None
+    oc = onchip_mask(b, args.pc, precision, db.solver.scaled_mapping()) if kern == 4 else None
+    ch = chip_mask(b, db.solver) if kern == 4 else None
     bytes_solve = float(algorithmic_bytes(b, res["iters"], res["outer"], args.pc, precision, kern, oc, ch).sum())
     split = None
     if kern == 4:
@@ -477,7 +471,7 @@ def main() -> int:
             r = db.results()
             pk = db.solver.solve_kernel()[0]
             oc = onchip_mask(b, pc, precision, db.solver.scaled_mapping()) if pk == 4 else None
-            ch = chip_mask(b, precision, is_default) if pk == 4 else None
+            ch = chip_mask(b, db.solver) if pk == 4 else None
             by = float(algorithmic_bytes(b, r["iters"], r["outer"], pc, precision, pk, oc, ch).sum())
             compare[pc] = {"iters_mean": round(float(r["iters"].mean()), 3),
                            "outer_mean": round(float(r["outer"].mean()), 3),
