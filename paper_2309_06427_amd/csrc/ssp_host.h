@@ -188,7 +188,8 @@ hipError_t launch_pcg3(const SolveArgs &a, bool fp32, int threads, int nx, int g
 // (with all six vectors there pcg4_lds(nx, N, true); -1: no such state size), at most kLds4Cap.
 constexpr int kLds4Cap = 160 * 1024 - 256;
 int64_t pcg4_lds(int nx, int N, bool all_vectors);
-hipError_t launch_pcg4(const SolveArgs &a, int nx, hipStream_t s);
+// `spare`: CUs it leaves to another grid.
+hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s);
 // LDS bytes for the largest pipeline step of state size nx at `threads`
 // with m Horner steps (0 if it cannot run), and the knots per step a budget
 // gives (< 1: cannot run).
