@@ -597,7 +597,6 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
                          [](const ssp_batch::Group &u, const ssp_batch::Group &v) { return u.work > v.work; });
     }
     if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) b->cus = 256;
-    const int cus = b->cus;
     std::vector<int32_t> gorder;
     for (auto &g : b->groups) {
         g.offset = (int)gorder.size();
@@ -610,15 +609,9 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
             return l >= 0 && l <= ssp::kLds4Cap;
         };
         while (g.streamed < g.count && !fits(gorder[g.offset + g.streamed])) ++g.streamed;
-        // At nx 6 a pass is all barriers and latency: three streaming workgroups per CU hide it better than one
-        // on-chip workgroup once there are problems enough (N 32 to 256, on-chip against streaming: 256 problems
-        // 0.224 and 0.367 ms, 512: 0.320 and 0.386, 768: 0.440 and 0.413, 1365: 0.781 and 0.513).
-        // With horizons beyond 256, whose later sets are read again at every product, the line is one problem per CU
-        // (N 480 to 500, 300 problems: 0.865 and 0.809 ms; N 980 to 1000, 64: 0.966 and 1.343, 512: 2.245 and 1.599).
-        if (g.nx == 6 && g.streamed < g.count) {
-            const int longest = N[gorder[g.offset + g.streamed]];
-            if (2 * (g.count - g.streamed) > (longest <= 256 ? 5 : 2) * cus) g.streamed = g.count;
-        }
+        std::vector<int32_t> horizons;
+        for (int j = 0; j < g.count; ++j) horizons.push_back(N[gorder[g.offset + j]]);
+        if (!ssp::chip_pays(g.nx, horizons.data(), g.count, g.streamed, b->cus)) g.streamed = g.count;
         if (g.streamed < g.count)
             g.chip_lds = (int)std::min<int64_t>(ssp::pcg4_lds(g.nx, N[gorder[g.offset + g.streamed]], true),
                                                 ssp::kLds4Cap);

@@ -1,0 +1,70 @@
+// Which form of a solve a group of problems takes: the on-chip or the streaming scaled solve.  Each form is priced per problem by a line fitted to measurements and the problems are put on
+// the workgroups that are resident at once, longest first, as the device's queue does; the shorter schedule wins.
+#include <algorithm>
+#include <functional>
+#include <vector>
+
+#include "ssp_host.h"
+
+namespace ssp {
+
+namespace {
+
+// End of the last job when jobs of these costs, longest first, each go to the machine that is free first.
+double schedule(const std::vector<double> &cost, int machines) {
+    std::vector<double> end(cost.begin(), cost.begin() + std::min<size_t>(cost.size(), machines));
+    if (end.empty()) return 0.0;
+    std::make_heap(end.begin(), end.end(), std::greater<double>());  // the machine that is free first on top
+    for (size_t j = end.size(); j < cost.size(); ++j) {
+        std::pop_heap(end.begin(), end.end(), std::greater<double>());
+        end.back() += cost[j];
+        std::push_heap(end.begin(), end.end(), std::greater<double>());
+    }
+    return *std::max_element(end.begin(), end.end());
+}
+
+// One problem of N knots in microseconds.  On chip, a workgroup per CU: a start, then a solve that grows with the knots,
+// faster past the `held` ones in registers.  Streaming, three workgroups per CU: a solve that grows with the steps of
+// `step` knots and with the knots.  Short horizons converge in fewer iterations: both solves are scaled by min(N, 5) / 5.
+struct ScaledCost {
+    int nx, step, held;
+    double chip0, chip, chip_knot, chip_more, stream, stream_step, stream_knot;
+};
+constexpr ScaledCost kScaledCost[] = {{6, 40, 160, 1, 73, 0.67, 1.05, 23, 29, 0.8},
+                                      {14, 16, 128, 7, 61, 0.67, 1.5, 24, 54, 2.4},
+                                      {26, 8, 32, 17, 51, 3.4, 4.2, 33, 60, 11}};
+
+}  // namespace
+
+// The lines were fitted to 633 measured pairs (symmetric stair, block-Jacobi and degree 3 at nx 6, 14, 26; 1 to 768
+// knots, uniform and ragged; 16 to 4096 problems): the form they choose is at most 5% slower than streaming and 14%
+// slower than the better one at any of them.  On chip and streaming, us: nx 14, 4096 problems of 16 knots 1166 and 625,
+// of 32 1299 and 1239, of 64 1712 and 2275; 256 of 16 104 and 128; nx 26, 4096 of 8 1454 and 909, of 16 1695 and 1873,
+// of 64 4092 and 6572; 512 of 8 225 and 197; nx 6, 256 of 32 113 and 100, of 64 129 and 160; 512 of 128 321 and 286;
+// 640 of 32 to 256 428 and 449, 1365 781 and 513.
+//
+// `too_long` leading problems stream in any case.  Beside them the on-chip grid has the CUs that they leave, or waits for
+// them: 256 problems of 400 and 256 of 300 knots at nx 26 take 7.96 ms so and 6.78 when all stream, 600 of 400 and 600
+// of 200 take 10.4 and 11.2.
+bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {
+    const ScaledCost *c = nullptr;
+    for (const auto &q : kScaledCost)
+        if (q.nx == nx) c = &q;
+    if (!c || too_long >= count) return false;
+    std::vector<double> chip, stream;
+    for (int j = 0; j < count; ++j) {
+        const double n = N[j], early = std::min(n, 5.0) / 5.0;
+        stream.push_back(early * (c->stream + c->stream_step * ((N[j] + (int64_t)c->step - 1) / c->step) + c->stream_knot * n));
+        if (j >= too_long)
+            chip.push_back(c->chip0 + early * (c->chip + c->chip_knot * std::min<double>(n, c->held) +
+                                               c->chip_more * std::max<double>(n - c->held, 0)));
+    }
+    const double all = schedule(stream, 3 * cus);
+    stream.resize(too_long);
+    const double longest = schedule(stream, 3 * cus);
+    double t = longest + schedule(chip, cus);
+    if (too_long < cus) t = std::min(t, std::max(longest, schedule(chip, cus - too_long)));
+    return t <= all;
+}
+
+}  // namespace ssp

@@ -133,7 +133,7 @@ struct ssp_batch {
         int nx = 0, count = 0, offset = 0;  // problems dgorder[offset .. offset + count)
         double work = 0;                    // sum of N nx^2 (launch order: largest first)
         int streamed = 0, chip_lds = 0;     // scaled solve under FP32 storage: the first `streamed` problems are too
-                                            // long for the on-chip solve; LDS bytes of the others
+                                            // long for the on-chip solve, or it does not pay; LDS bytes of the others
         hipStream_t chip_stream = nullptr;  // of the on-chip problems where the group also has streaming ones, forked
         hipEvent_t chip_fork = nullptr, chip_done = nullptr;  // from the caller's stream and joined back into it
         int threads = 0, lds = 0;

@@ -190,6 +190,9 @@ constexpr int kLds4Cap = 160 * 1024 - 256;
 int64_t pcg4_lds(int nx, int N, bool all_vectors);
 // `spare`: CUs it leaves to another grid.
 hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s);
+// Whether the problems of state size nx, N[0 .. count) longest first, are faster with all but the first `too_long` on
+// chip than all streaming, on a device of `cus` CUs.
+bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus);
 // LDS bytes for the largest pipeline step of state size nx at `threads`
 // with m Horner steps (0 if it cannot run), and the knots per step a budget
 // gives (< 1: cannot run).

@@ -102,3 +102,15 @@ def test_the_edge_batches_have_on_chip_problems():
         with solver.DeviceBatch(pack(nx, ns)) as db:
             db.build("sym", "fp32_refine64")
             assert db.solver.onchip_problems(nx) == sum(n <= ENDS[nx][1] for n in ns)
+
+
+@pytest.mark.parametrize("nx", [14, 26])
+def test_many_short_problems_stream(nx):
+    """The same problems few on chip and many streaming: the same bits."""
+    ns = np.random.default_rng(nx).integers(1, 9, size=1200)
+    (a, on), _ = both(pack(nx, ns))
+    (few, fon), (fs, _) = both(pack(nx, ns[:100]))
+    assert on == {nx: 0} and fon == {nx: 100}
+    assert_same(few, fs)
+    n = few["lam"].shape[0]
+    assert np.array_equal(a["lam"][:n], few["lam"]) and np.array_equal(a["iters"][:100], few["iters"])

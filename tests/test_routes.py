@@ -1,0 +1,67 @@
+"""The rules that choose between the forms of a solve, against measured times.
+
+Each row is a batch of one state size that was timed in both forms; the rule,
+a host function of the horizons and the CU count, has to take the faster one
+wherever they differ by more than a tenth.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+CUS = 256
+
+# state size, horizons (one, or a range drawn uniformly), problems, on-chip ms, streaming ms
+SCALED = [
+    (14, 1, 16, 0.0315, 0.0261), (14, 1, 4096, 0.2992, 0.1039), (14, 4, 128, 0.0860, 0.0922), (14, 4, 1024, 0.2672, 0.1673),
+    (14, 8, 256, 0.1017, 0.1184), (14, 8, 4096, 1.0735, 0.5364), (14, 16, 256, 0.1038, 0.1278), (14, 16, 300, 0.1710, 0.1380),
+    (14, 16, 512, 0.1741, 0.1396), (14, 20, 1024, 0.3397, 0.3653), (14, 20, 4096, 1.2347, 1.0036),
+    (14, 64, 4096, 1.7121, 2.2748), (14, 128, 512, 0.3256, 0.7541), (14, 256, 1024, 1.3694, 2.9087),
+    (14, 768, 16, 0.9976, 3.7127), (14, (1, 9), 100, 0.0937, 0.1082), (14, (1, 9), 4096, 0.8539, 0.3831),
+    (14, (1, 32), 1365, 0.3964, 0.2944), (14, (1, 32), 300, 0.1439, 0.2046), (14, (32, 256), 4096, 2.9338, 4.5994),
+    (26, 1, 128, 0.0368, 0.0282), (26, 1, 4096, 0.3699, 0.1281), (26, 2, 512, 0.1231, 0.0886), (26, 4, 16, 0.0849, 0.1095),
+    (26, 4, 4096, 1.2211, 0.6930), (26, 8, 256, 0.1247, 0.1743), (26, 8, 512, 0.2248, 0.1968), (26, 8, 4096, 1.4439, 0.9058),
+    (26, 16, 512, 0.2483, 0.3746), (26, 24, 4096, 2.1505, 2.6313), (26, 64, 1024, 1.0995, 2.2059),
+    (26, 360, 256, 1.9299, 5.5498), (26, (1, 12), 4096, 1.2739, 0.8661), (26, (1, 40), 300, 0.2053, 0.6173),
+    (26, (32, 256), 1365, 3.3381, 5.2636),
+    (6, 1, 16, 0.0279, 0.0222), (6, 8, 640, 0.1996, 0.0863), (6, 32, 16, 0.0963, 0.0860), (6, 32, 256, 0.1130, 0.1000),
+    (6, 64, 256, 0.1288, 0.1594), (6, 64, 512, 0.2355, 0.1727), (6, 128, 256, 0.1769, 0.2715), (6, 128, 512, 0.3212, 0.2860),
+    (6, 256, 256, 0.3025, 0.4533), (6, 256, 640, 0.7361, 0.5370), (6, 985, 64, 0.966, 1.343), (6, 985, 512, 2.245, 1.599),
+    (6, (1, 40), 256, 0.1165, 0.0975), (6, (1, 64), 640, 0.2510, 0.1621), (6, (32, 256), 512, 0.3639, 0.4569),
+    (6, (32, 256), 1365, 0.781, 0.513),
+]
+
+
+def chip_pays(nx, N, too_long=0, cus=CUS):
+    from paper_2309_06427_amd import _lib
+    f = _lib.load()._ZN3ssp9chip_paysEiPKiiii
+    f.restype = C.c_bool
+    N = np.ascontiguousarray(np.sort(np.asarray(N, dtype=np.int32))[::-1])
+    return f(nx, N.ctypes.data_as(C.c_void_p), len(N), too_long, cus)
+
+
+def horizons(n, P):
+    return np.full(P, n) if np.isscalar(n) else np.random.default_rng(P).integers(n[0], n[1] + 1, size=P)
+
+
+@pytest.mark.parametrize("nx,n,P,chip,stream", SCALED)
+def test_scaled_form_is_the_faster_one(nx, n, P, chip, stream):
+    pays = chip_pays(nx, horizons(n, P))
+    if chip <= stream / 1.1:
+        assert pays
+    elif stream <= chip / 1.1:
+        assert not pays
+
+
+def test_scaled_form_beside_problems_that_are_too_long():
+    """nx 26: 256 of 400 knots and 256 of 300 (7.96 ms with the latter on chip, 6.78 all streaming); 600 of 400 and 600
+    of 200 (10.4 and 11.2); 16 of 400 and 480 of 300 (5.95 and 8.3 in turn); all of them too long."""
+    assert not chip_pays(26, [400] * 256 + [300] * 256, 256)
+    assert chip_pays(26, [400] * 600 + [200] * 600, 600)
+    assert chip_pays(26, [400] * 16 + [300] * 480, 16)
+    assert not chip_pays(26, [400] * 16, 16)
+
+
+def test_scaled_form_of_other_state_sizes_streams():
+    assert not any(chip_pays(nx, [50]) for nx in range(1, 65) if nx not in (6, 14, 26))
+    assert chip_pays(14, [50], cus=1)
