@@ -141,18 +141,10 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
 
 // Workgroup size and LDS bytes of the fused kernel for one solve group, or
 // lds = 0 if its knots do not fit the fused kernel's registers or LDS.
-//
-// FP64 without a chosen mapping: one workgroup of 512 threads per CU, whose step holds 6 to 80 knots of a problem,
-// where 128 threads hold one knot of 26 states, half a wave's work between two barriers.  Only where a small state
-// size leaves several small workgroups per CU with problems of their own are 256 threads better.  Measured, 128 /
-// 256 / 512 threads in ms: nx 26 x 1024 problems of condition 1e6 156 / 120 / 53, x 16 16.4 / 8.1 / 2.4; nx 20 x 512
-// 14.6 / 7.8 / 3.9; nx 14 x 1024 3.77 / 3.07 / 2.71, x 2500 - / 7.32 / 6.63, x 16 2.67 / 1.49 / 0.75; nx 13 x 1024
-// - / 4.28 / 4.05; nx 12 x 1024 - / 3.28 / 3.24, x 600 - / 2.00 / 2.16; nx 10 x 1024 - / 2.22 / 2.48; nx 9 x 512
-// 1.75 / 0.98 / 1.05; nx 6 x 1024 0.90 / 0.90 / 1.14, x 16 0.69 / 0.45 / 0.31.
 void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, int *lds) {
     const bool chosen = g.threads > 0 || b->mapping_set;
     int t = g.threads > 0 ? g.threads : b->threads;
-    if (!chosen && !b->fp32) t = g.nx < 13 && g.count > 2 * b->cus ? 256 : 512;
+    if (!chosen && !b->fp32) t = g.fp64_threads;
     *threads = t;
     *lds = 0;
     if (!ssp::pcg2_threads_ok(t) && (chosen || t != 512)) return;
@@ -597,7 +589,7 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
                          [](const ssp_batch::Group &u, const ssp_batch::Group &v) { return u.work > v.work; });
     }
     if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) b->cus = 256;
-    std::vector<int32_t> gorder;
+    std::vector<int32_t> gorder, horizons;  // problems group by group, longest first, and their horizons
     for (auto &g : b->groups) {
         g.offset = (int)gorder.size();
         for (int32_t p : order)
@@ -609,9 +601,8 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
             return l >= 0 && l <= ssp::kLds4Cap;
         };
         while (g.streamed < g.count && !fits(gorder[g.offset + g.streamed])) ++g.streamed;
-        std::vector<int32_t> horizons;
         for (int j = 0; j < g.count; ++j) horizons.push_back(N[gorder[g.offset + j]]);
-        if (!ssp::chip_pays(g.nx, horizons.data(), g.count, g.streamed, b->cus)) g.streamed = g.count;
+        if (!ssp::chip_pays(g.nx, horizons.data() + g.offset, g.count, g.streamed, b->cus)) g.streamed = g.count;
         if (g.streamed < g.count)
             g.chip_lds = (int)std::min<int64_t>(ssp::pcg4_lds(g.nx, N[gorder[g.offset + g.streamed]], true),
                                                 ssp::kLds4Cap);
@@ -662,6 +653,12 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
     }
 
     DevGuard g(device);
+    for (auto &gr : b->groups) {
+        int32_t resident[3];
+        for (int q = 0; q < 3; ++q)
+            resident[q] = ssp::pcg2_fp64_resident(gr.nx, 128 << q, ssp::pcg2_lds(gr.nx, false, 128 << q));
+        gr.fp64_threads = ssp::fused_fp64_threads(gr.nx, horizons.data() + gr.offset, gr.count, b->cus, resident);
+    }
     ssp_status rc = SSP_OK;
     auto up = [&](auto **dst, const auto *src, size_t cnt) {
         if (rc != SSP_OK) return;

@@ -614,24 +614,59 @@ int pcg2_lds(int nx_max, bool fp32, int threads) {
     return bytes;
 }
 
+// All the LDS a workgroup may have is allowed once; each launch asks for its own size (launches of other sizes may be in
+// flight on other streams).
 template <typename TI, int BLOCK, int NX>
-static hipError_t launch2_t(const SolveArgs &a, int nprob, hipStream_t s) {
-    // all the LDS a workgroup may have is allowed once; each launch asks for
-    // its own size (launches of other sizes may be in flight on other streams)
-    static int allowed = 0;
+static hipError_t allow2_t(int *allowed) {
+    static int cap = 0;
     const void *f = (const void *)k_pcg2<TI, BLOCK, NX>;
-    if (allowed == 0) {
+    if (cap == 0) {
         hipFuncAttributes fa;
         hipError_t e = hipFuncGetAttributes(&fa, f);
         if (e != hipSuccess) return e;
-        const int cap = 160 * 1024 - (int)fa.sharedSizeBytes;
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+        const int c = 160 * 1024 - (int)fa.sharedSizeBytes;
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c);
         if (e != hipSuccess) return e;
-        allowed = cap;
+        cap = c;
     }
+    *allowed = cap;
+    return hipSuccess;
+}
+
+template <typename TI, int BLOCK, int NX>
+static hipError_t launch2_t(const SolveArgs &a, int nprob, hipStream_t s) {
+    int allowed = 0;
+    hipError_t e = allow2_t<TI, BLOCK, NX>(&allowed);
+    if (e != hipSuccess) return e;
     if (a.lds_bytes > allowed) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_pcg2<TI, BLOCK, NX>), dim3(nprob), dim3(BLOCK), a.lds_bytes, s, a);
     return hipGetLastError();
+}
+
+template <int BLOCK, int NX>
+static int resident2_t(int lds_bytes) {
+    int allowed = 0, n = 0;
+    if (allow2_t<double, BLOCK, NX>(&allowed) != hipSuccess || lds_bytes > allowed) return 0;
+    const void *f = (const void *)k_pcg2<double, BLOCK, NX>;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, BLOCK, (size_t)lds_bytes) == hipSuccess ? n : 0;
+}
+template <int BLOCK>
+static int resident2_nx(int nx, int lds_bytes) {
+    switch (nx) {
+        case 6: return resident2_t<BLOCK, 6>(lds_bytes);
+        case 14: return resident2_t<BLOCK, 14>(lds_bytes);
+        case 26: return resident2_t<BLOCK, 26>(lds_bytes);
+        case 36: return resident2_t<BLOCK, 36>(lds_bytes);
+        default: return resident2_t<BLOCK, 0>(lds_bytes);
+    }
+}
+int pcg2_fp64_resident(int nx, int threads, int lds_bytes) {
+    switch (threads) {
+        case 128: return resident2_nx<128>(nx, lds_bytes);
+        case 256: return resident2_nx<256>(nx, lds_bytes);
+        case 512: return resident2_nx<512>(nx, lds_bytes);
+    }
+    return 0;
 }
 
 template <typename TI, int BLOCK>

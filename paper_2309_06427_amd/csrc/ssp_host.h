@@ -173,6 +173,8 @@ hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, in
 int pcg2_lds(int nx_max, bool fp32, int threads);  // 0 if the mapping cannot hold one knot
 // The most it may be: what the kernel's reduction scratch (five values a wave) leaves of a CU's 160 KiB.
 int pcg2_lds_cap(bool fp32, int threads);
+// Workgroups of the FP64 fused kernel that a CU of the current device holds (0: none, or not known).
+int pcg2_fp64_resident(int nx, int threads, int lds_bytes);
 // Knots per step the fused kernel uses for state size nx (< 1: cannot run).
 int pcg2_steps_for(int nx, bool fp32, int threads, int lds_bytes);
 // Workgroup sizes a mapping may name (128, 256); the FP64 kernel is also compiled for 512, its default.
@@ -193,6 +195,9 @@ hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s);
 // Whether the problems of state size nx, N[0 .. count) longest first, are faster with all but the first `too_long` on
 // chip than all streaming, on a device of `cus` CUs.
 bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus);
+// Workgroup size of the FP64 fused solve for such problems where no mapping was chosen; resident: workgroups of 128, 256
+// and 512 threads that a CU holds.
+int fused_fp64_threads(int nx, const int32_t *N, int count, int cus, const int32_t *resident);
 // LDS bytes for the largest pipeline step of state size nx at `threads`
 // with m Horner steps (0 if it cannot run), and the knots per step a budget
 // gives (< 1: cannot run).

@@ -65,3 +65,39 @@ def test_scaled_form_beside_problems_that_are_too_long():
 def test_scaled_form_of_other_state_sizes_streams():
     assert not any(chip_pays(nx, [50]) for nx in range(1, 65) if nx not in (6, 14, 26))
     assert chip_pays(14, [50], cus=1)
+
+
+# state size, horizon, problems, ms with 128, 256 and 512 threads
+FUSED64 = [
+    (4, 1, 16, 0.0199, 0.0210, 0.0238), (4, 16, 512, 0.1359, 0.1455, 0.3248), (4, 128, 16, 0.6151, 0.3814, 0.2542),
+    (6, 8, 256, 0.0886, 0.0935, 0.1077), (6, 32, 512, 0.2661, 0.1718, 0.3124), (6, 128, 16, 0.7287, 0.4712, 0.3213),
+    (6, 128, 512, 0.8983, 0.5967, 0.6917), (9, 16, 256, 0.3349, 0.1991, 0.2511), (9, 64, 512, 1.2822, 0.6905, 1.0342),
+    (12, 2, 512, 0.0934, 0.0970, 0.2147), (12, 16, 16, 0.5064, 0.3577, 0.2531), (12, 16, 512, 0.5907, 0.4177, 0.5223),
+    (14, 4, 4096, 0.5220, 0.9069, 1.9643), (14, 8, 512, 0.2639, 0.1709, 0.3335), (14, 16, 4096, 2.3045, 2.2709, 2.7656),
+    (14, 128, 16, 2.9646, 1.5888, 0.8137), (14, 64, 512, 1.8698, 1.0765, 0.9837), (20, 2, 4096, 0.5227, 0.7828, 2.4258),
+    (20, 4, 256, 0.3080, 0.2183, 0.2662), (20, 32, 1024, 3.7489, 3.7964, 2.7684), (26, 2, 4096, 0.5842, 0.7967, 1.7290),
+    (26, 4, 512, 0.4178, 0.2670, 0.3764), (26, 8, 4096, 4.8723, 4.6218, 3.3787), (26, 128, 512, 20.45, 10.87, 5.806),
+    (31, 2, 512, 0.2625, 0.2103, 0.4444), (31, 8, 4096, 12.8155, 9.5538, 12.0855), (31, 64, 256, 19.28, 9.881, 3.997),
+]
+
+
+def fp64_threads(nx, N, resident):
+    from paper_2309_06427_amd import _lib
+    f = _lib.load()._ZN3ssp18fused_fp64_threadsEiPKiiiS1_
+    N = np.ascontiguousarray(N, dtype=np.int32)
+    return f(nx, N.ctypes.data_as(C.c_void_p), len(N), CUS, (C.c_int32 * 3)(*resident))
+
+
+@pytest.mark.parametrize("nx,n,P,t128,t256,t512", FUSED64)
+def test_fp64_workgroup_is_close_to_the_fastest(nx, n, P, t128, t256, t512):
+    """Within a seventh of the fastest workgroup size."""
+    N = np.full(P, n, dtype=np.int32)
+    ms = {128: t128, 256: t256, 512: t512}
+    assert ms[fp64_threads(nx, N, (4, 2, 1) if nx in (6, 14, 26) else (5, 3, 1))] <= min(ms.values()) * 8 / 7
+
+
+def test_fp64_workgroup_of_sizes_that_few_hold():
+    """From state size 45 on only 512 threads hold a knot, from 58 on none does (the explicit kernel's 128)."""
+    N = np.full(3, 1, dtype=np.int32)
+    got = [fp64_threads(nx, N, (1, 1, 1)) for nx in (44, 45, 57, 58, 64)]
+    assert got == [256, 512, 512, 128, 128]
