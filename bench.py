@@ -331,7 +331,7 @@ def main() -> int:
     db = solver.DeviceBatch(b)
     db.solver.set_keep_inverses(args.keep_inverses)
     if args.threads or args.kernel:
-        db.solver.set_mapping(args.threads or 128, args.lds, args.kernel)
+        db.solver.set_mapping(args.threads or (128 if args.lds else 0), args.lds, args.kernel)
     stream = torch.cuda.current_stream()
     mapping = None
     db.build(args.pc, precision)

@@ -254,8 +254,9 @@ ssp_status ssp_solve_outer(const ssp_batch *b, int32_t *outer, void *stream);
 ssp_status ssp_export(ssp_batch *b, int which, double *diag, double *off, void *stream);
 
 /* Kernel-mapping knobs of the batched PCG kernel (the autotuner sets them):
- * threads per workgroup (64, 128, 256 or 512), the LDS staging budget in
- * bytes per workgroup (0 = library default) and the kernel:
+ * threads per workgroup (64, 128, 256 or 512; 0, with a budget of 0, gives
+ * the library's own mapping back), the LDS staging budget in bytes per
+ * workgroup (0 = library default) and the kernel:
  *   0 = automatic (default): a batch of one problem with N >= 24 knots runs
  *       the cooperative solve when its grid fits on the device at once, any
  *       other batch the fused kernel;
@@ -274,8 +275,9 @@ ssp_status ssp_export(ssp_batch *b, int which, double *diag, double *off, void *
  *       block-Jacobi and both stairs under FP32 storage (except a single
  *       problem of N >= 24 knots, which runs the cooperative solve).
  * The choice takes effect at the next build.
- * The fused kernel is built for 128 and 256 threads (FP64 storage also for
- * 512, its default until a mapping is set) and for knots that fit
+ * The fused kernel is built for 128 and 256 threads, under FP64 storage also
+ * for 512 (chosen by the library's own mapping or ssp_set_group_mapping; 512
+ * given here select the explicit kernel), and for knots that fit
  * its LDS rings; otherwise the explicit kernel runs.  Returns SSP_ERR_ARG for
  * an unknown value or a budget that cannot hold one knot of the largest nx. */
 ssp_status ssp_set_mapping(ssp_batch *b, int32_t threads, int32_t lds_bytes, int32_t kernel);
@@ -345,8 +347,8 @@ ssp_status ssp_gemm_f32(int32_t M, int32_t N, int32_t K, const float *A, int32_t
  * in groups of one state size, each group launched on its own stream with its
  * own workgroup size and LDS budget (the budget sets the knots per pipeline
  * step, hence workgroups per CU).  ssp_autotune times every candidate
- * mapping (the FP64 default; 128 or 256 threads; the largest step and two shorter ones) on
- * each group alone with this batch's last build and keeps the fastest; it
+ * mapping (128, 256 or, under FP64 storage, 512 threads; the largest step and
+ * two shorter ones) on each group alone with this batch's last build and keeps the fastest; it
  * then solves the whole batch once, so the outputs (same meaning as in
  * ssp_solve, zero start, max_iter = 10 N nx) hold valid results.  It
  * synchronises the stream and must not be captured into a graph.
@@ -355,10 +357,11 @@ ssp_status ssp_gemm_f32(int32_t M, int32_t N, int32_t K, const float *A, int32_t
 ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, double *lambda, int32_t *iters,
                         double *relres, int32_t *prob_status, void *stream);
 /* Set the fused kernel's mapping of the solve group with state size nx
- * (e.g. a mapping the autotuner found earlier): threads 128 or 256 and an
- * LDS budget that holds at least one pipeline step; 0, 0 restores the
- * default.  The storage precision of the next ssp_build must be the one the
- * budget was checked for (checked against the current storage).
+ * (e.g. one that ssp_get_mapping reported): threads 128, 256 or, under FP64
+ * storage, 512, and an LDS budget that holds at least one pipeline step; 0, 0
+ * restores the handle's.  The storage precision of the next ssp_build must be
+ * the one the budget was checked for (checked against the current storage;
+ * 512 threads do not apply under FP32 storage).
  * SSP_ERR_ARG for an unknown nx or an unusable mapping. */
 ssp_status ssp_set_group_mapping(ssp_batch *b, int32_t nx, int32_t threads, int32_t lds_bytes);
 /* The mapping in use per solve group (largest total work first): up to

@@ -142,15 +142,16 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
 // Workgroup size and LDS bytes of the fused kernel for one solve group, or
 // lds = 0 if its knots do not fit the fused kernel's registers or LDS.
 void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, int *lds) {
-    const bool chosen = g.threads > 0 || b->mapping_set;
-    int t = g.threads > 0 ? g.threads : b->threads;
-    if (!chosen && !b->fp32) t = g.fp64_threads;
+    const bool own = g.threads > 0 && ssp::pcg2_threads_ok(b->fp32, g.threads);  // 512 threads are for FP64 storage
+    int t = own ? g.threads : b->threads;
+    if (!own && !b->mapping_set && !b->fp32) t = g.fp64_threads;
     *threads = t;
     *lds = 0;
-    if (!ssp::pcg2_threads_ok(t) && (chosen || t != 512)) return;
+    // 512 threads given for the whole handle select the explicit kernel
+    if (!ssp::pcg2_threads_ok(b->fp32, t) || (t == 512 && !own && b->mapping_set)) return;
     const int need = ssp::pcg2_lds(g.nx, b->fp32, t);
     if (need == 0) return;
-    int l = g.lds > 0 ? g.lds : (b->lds_bytes > 0 ? b->lds_bytes : need);
+    int l = own ? g.lds : (b->lds_bytes > 0 ? b->lds_bytes : need);
     l = std::max(l, ssp::bt_sweep_min_lds(g.nx, true, 8));
     if (l > ssp::pcg2_lds_cap(b->fp32, t)) return;
     if (ssp::pcg2_steps_for(g.nx, b->fp32, t, l) < 1) return;
@@ -386,7 +387,7 @@ std::vector<int> lds_candidates(const ssp_batch *b, int nx, int threads) {
     for (int c : {cmax, cmax - 1, (cmax + 1) / 2}) {
         if (c < 1) continue;
         const int l = std::max((c + 2) * per + nxp * eb + 16, lo);
-        if (l <= ssp::kFusedLdsCap && ssp::pcg2_steps_for(nx, b->fp32, threads, l) >= 1 &&
+        if (l <= ssp::pcg2_lds_cap(b->fp32, threads) && ssp::pcg2_steps_for(nx, b->fp32, threads, l) >= 1 &&
             std::find(out.begin(), out.end(), l) == out.end())
             out.push_back(l);
     }
@@ -794,12 +795,12 @@ ssp_status ssp_layout(const ssp_batch *b, int64_t *off_nn, int64_t *off_nu, int6
 
 ssp_status ssp_set_mapping(ssp_batch *b, int32_t threads, int32_t lds_bytes, int32_t kernel) {
     if (!b) return SSP_ERR_ARG;
-    if (threads != 64 && threads != 128 && threads != 256 && threads != 512) return SSP_ERR_ARG;
-    if (lds_bytes < 0 || lds_bytes > 160 * 1024) return SSP_ERR_ARG;
+    if (threads != 0 && threads != 64 && threads != 128 && threads != 256 && threads != 512) return SSP_ERR_ARG;
+    if (lds_bytes < 0 || lds_bytes > 160 * 1024 || (threads == 0 && lds_bytes != 0)) return SSP_ERR_ARG;
     if (kernel < 0 || kernel > 4) return SSP_ERR_ARG;
     if (lds_bytes > 0 && lds_bytes < ssp::pcg_min_lds(b->nx_max, true)) return SSP_ERR_ARG;
-    b->threads = threads;
-    b->mapping_set = true;
+    b->threads = threads ? threads : 128;
+    b->mapping_set = threads != 0;
     b->lds_bytes = lds_bytes;
     b->kernel = kernel;
     for (auto &g : b->groups) g.threads = g.lds = 0;
@@ -1073,9 +1074,9 @@ ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, doubl
         auto &g = b->groups[gi];
         int best_t = 0, best_l = 0;
         float best = 0.0f;
-        for (int t : {0, 128, 256}) {  // 0: the default mapping
-            if (t == 0 && (b->fp32 || b->mapping_set)) continue;  // there one of the candidates below
-            for (int l : t ? lds_candidates(b, g.nx, t) : std::vector<int>{0}) {
+        for (int t : {128, 256, 512}) {
+            if (!ssp::pcg2_threads_ok(b->fp32, t)) continue;
+            for (int l : lds_candidates(b, g.nx, t)) {
                 g.threads = t;
                 g.lds = l;
                 float ms = 0.0f;
@@ -1091,7 +1092,7 @@ ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, doubl
                         fail(e, "autotune timing");
                 }
                 if (rc != SSP_OK) break;
-                if (best == 0.0f || ms < best) {
+                if (best_t == 0 || ms < best) {
                     best = ms;
                     best_t = t;
                     best_l = l;
@@ -1123,8 +1124,8 @@ ssp_status ssp_set_group_mapping(ssp_batch *b, int32_t nx, int32_t threads, int3
             g.threads = g.lds = 0;
             return SSP_OK;
         }
-        if (!ssp::pcg2_threads_ok(threads) || lds_bytes < ssp::bt_sweep_min_lds(nx, true, 8) ||
-            lds_bytes > ssp::kFusedLdsCap || ssp::pcg2_steps_for(nx, b->fp32, threads, lds_bytes) < 1)
+        if (!ssp::pcg2_threads_ok(b->fp32, threads) || lds_bytes < ssp::bt_sweep_min_lds(nx, true, 8) ||
+            lds_bytes > ssp::pcg2_lds_cap(b->fp32, threads) || ssp::pcg2_steps_for(nx, b->fp32, threads, lds_bytes) < 1)
             return SSP_ERR_ARG;
         g.threads = threads;
         g.lds = lds_bytes;

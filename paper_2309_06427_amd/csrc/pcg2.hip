@@ -680,7 +680,7 @@ static hipError_t launch2_nx(const SolveArgs &a, int nprob, int nx, hipStream_t 
     }
 }
 
-bool pcg2_threads_ok(int threads) { return threads == 128 || threads == 256; }
+bool pcg2_threads_ok(bool fp32, int threads) { return threads == 128 || threads == 256 || (threads == 512 && !fp32); }
 
 hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, int nx, hipStream_t s) {
     if (nprob == 0) return hipSuccess;

@@ -115,7 +115,7 @@ struct ssp_batch {
     ssp_precon pc = SSP_PC_SYM_STAIR;
     ssp_precision prec = SSP_FP64;
     int threads = 128;
-    bool mapping_set = false;  // threads came from ssp_set_mapping
+    bool mapping_set = false;  // threads, lds_bytes came from ssp_set_mapping
     int cus = 256;
     int lds_bytes = 0;  // 0: default
     int kernel = 0;     // 0 auto, 1 explicit, 2 batched fused, 3 cooperative (one problem), 4 scaled

@@ -177,8 +177,8 @@ int pcg2_lds_cap(bool fp32, int threads);
 int pcg2_fp64_resident(int nx, int threads, int lds_bytes);
 // Knots per step the fused kernel uses for state size nx (< 1: cannot run).
 int pcg2_steps_for(int nx, bool fp32, int threads, int lds_bytes);
-// Workgroup sizes a mapping may name (128, 256); the FP64 kernel is also compiled for 512, its default.
-bool pcg2_threads_ok(int threads);
+// Workgroup sizes the fused kernel is compiled for (128, 256; 512 under FP64 storage).
+bool pcg2_threads_ok(bool fp32, int threads);
 
 // Scaled solve of the problems order[0 .. nprob) (all of state size nx, one
 // of kBuildSizes): one persistent grid of the kernel instance compiled for

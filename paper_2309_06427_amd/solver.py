@@ -285,9 +285,7 @@ class DeviceBatch:
             t, l = self.solver.scaled_mapping()[:2]
             entry = {"kind": "scaled", "threads": t, "lds": l}
         else:
-            # workgroups of 512 threads are the default mapping of a group, stored as 0, 0
-            entry = {"kind": "groups", "groups": [[nx, 0, 0] if t == 512 else [nx, t, l]
-                                                  for nx, t, l, _ in self.solver.mapping()]}
+            entry = {"kind": "groups", "groups": [[nx, t, l] for nx, t, l, _ in self.solver.mapping()]}
         try:
             with open(path) as f:
                 data = json.load(f)
