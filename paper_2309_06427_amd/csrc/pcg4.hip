@@ -80,14 +80,11 @@ __host__ __device__ inline int64_t lds4_bytes(int N, int nvec) {
     return 4 * (int64_t)(waves4<NX>() * scratch4<NX>() + (waves4<NX>() + 1) * 32) + 4 * (int64_t)nvec * vec4_floats<NX>(N);
 }
 
-template <int J>
-struct DppChain;
-
 #define SSP_FMAC_B(s, x, a, l) "v_fmac_f32_dpp " s ", " x ", " a " row_newbcast:" l " row_mask:0xf bank_mask:0xf\n\t"
 
 // s0 += sum of the even terms, s1 += sum of the odd terms of a[0 .. n) x(lane 0 .. n - 1 of the 16-lane group), in
-// order (n = 13; O = 1: term 0 is odd).  The leading wait covers a VALU write of x just before (two wait states for
-// a DPP read).
+// order (n = 13; O = 1: term 0 is odd).  The sums are written before the last inputs are read (early-clobber operands).
+// The leading wait covers a VALU write of x just before (two wait states for a DPP read).
 template <int O>
 __device__ __forceinline__ void chain13(const float *a, float x, float &s0, float &s1) {
     float &e = O ? s1 : s0, &o = O ? s0 : s1;
@@ -97,7 +94,7 @@ __device__ __forceinline__ void chain13(const float *a, float x, float &s0, floa
                     SSP_FMAC_B("%0", "%2", "%11", "8") SSP_FMAC_B("%1", "%2", "%12", "9")
                         SSP_FMAC_B("%0", "%2", "%13", "10") SSP_FMAC_B("%1", "%2", "%14", "11")
                             SSP_FMAC_B("%0", "%2", "%15", "12") "s_nop 0"
-        : "+v"(e), "+v"(o)
+        : "+&v"(e), "+&v"(o)
         : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]),
           "v"(a[9]), "v"(a[10]), "v"(a[11]), "v"(a[12]));
 }
@@ -108,7 +105,7 @@ __device__ __forceinline__ void chain14(const float *a, float x, float &s0, floa
                     SSP_FMAC_B("%0", "%2", "%11", "8") SSP_FMAC_B("%1", "%2", "%12", "9")
                         SSP_FMAC_B("%0", "%2", "%13", "10") SSP_FMAC_B("%1", "%2", "%14", "11")
                             SSP_FMAC_B("%0", "%2", "%15", "12") SSP_FMAC_B("%1", "%2", "%16", "13") "s_nop 0"
-        : "+v"(s0), "+v"(s1)
+        : "+&v"(s0), "+&v"(s1)
         : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]),
           "v"(a[9]), "v"(a[10]), "v"(a[11]), "v"(a[12]), "v"(a[13]));
 }
@@ -116,7 +113,7 @@ __device__ __forceinline__ void chain6(const float *a, float x, float &s0, float
     asm("s_nop 1\n\t" SSP_FMAC_B("%0", "%2", "%3", "0") SSP_FMAC_B("%1", "%2", "%4", "1")
             SSP_FMAC_B("%0", "%2", "%5", "2") SSP_FMAC_B("%1", "%2", "%6", "3") SSP_FMAC_B("%0", "%2", "%7", "4")
                 SSP_FMAC_B("%1", "%2", "%8", "5") "s_nop 0"
-        : "+v"(s0), "+v"(s1)
+        : "+&v"(s0), "+&v"(s1)
         : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]));
 }
 #undef SSP_FMAC_B
