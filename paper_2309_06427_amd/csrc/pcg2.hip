@@ -614,22 +614,22 @@ int pcg2_lds(int nx_max, bool fp32, int threads) {
     return bytes;
 }
 
-// All the LDS a workgroup may have is allowed once; each launch asks for its own size (launches of other sizes may be in
-// flight on other streams).
+// All the LDS a workgroup may have is allowed once per device; each launch asks for its own size (launches of other sizes
+// may be in flight on other streams).
 template <typename TI, int BLOCK, int NX>
 static hipError_t allow2_t(int *allowed) {
-    static int cap = 0;
+    static PerDevice cap;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    *allowed = cap.get(dev);
+    if (*allowed) return hipSuccess;
     const void *f = (const void *)k_pcg2<TI, BLOCK, NX>;
-    if (cap == 0) {
-        hipFuncAttributes fa;
-        hipError_t e = hipFuncGetAttributes(&fa, f);
-        if (e != hipSuccess) return e;
-        const int c = 160 * 1024 - (int)fa.sharedSizeBytes;
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c);
-        if (e != hipSuccess) return e;
-        cap = c;
-    }
-    *allowed = cap;
+    hipFuncAttributes fa;
+    if ((e = hipFuncGetAttributes(&fa, f)) != hipSuccess) return e;
+    *allowed = 160 * 1024 - (int)fa.sharedSizeBytes;
+    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, *allowed)) != hipSuccess) return e;
+    cap.set(dev, *allowed);
     return hipSuccess;
 }
 

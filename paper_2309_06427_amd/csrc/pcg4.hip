@@ -27,8 +27,6 @@
 // steps and summed by the same trees (dots4), so both solves return the same bits.
 #include <math.h>
 
-#include <atomic>
-
 #include "ssp_device.h"
 #include "ssp_fused.h"
 #include "ssp_host.h"
@@ -1089,24 +1087,25 @@ hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s) {
     const void *f = pcg4_kernel(nx);
     if (!f) return hipErrorInvalidValue;
     const int block = nx == 6 ? block4<6>() : nx == 14 ? block4<14>() : block4<26>();
-    // the LDS opt-in and the CU count once per process and kernel (no runtime query inside a graph capture after
-    // the first eager solve); a race sets the same values twice
-    static std::atomic<int> cus[65];
-    int n = cus[nx].load();
+    // the LDS opt-in and the CU count once per kernel and device (no runtime query of either inside a graph capture after
+    // the first eager solve)
+    static PerDevice cus[3];
+    PerDevice &known = cus[nx == 6 ? 0 : nx == 14 ? 1 : 2];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    int n = known.get(dev);
     if (n == 0) {
-        hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLds4Cap);
-        if (e != hipSuccess) return e;
-        int dev = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+        if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLds4Cap)) != hipSuccess) return e;
         if ((e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        cus[nx].store(n);
+        known.set(dev, n);
     }
     // workgroups that fit a CU together: by registers (two waves per SIMD) and LDS
     const int by_lds = 160 * 1024 / (a.lds_bytes + 256), by_reg = 512 / block;
     n = (n > spare ? n - spare : 1) * (by_lds < by_reg ? by_lds : by_reg);
     SolveArgs arg = a;
     void *args[] = {(void *)&arg};
-    hipError_t e = hipLaunchKernel(f, dim3(n < a.nprob ? n : a.nprob), dim3(block), args, (size_t)a.lds_bytes, s);
+    e = hipLaunchKernel(f, dim3(n < a.nprob ? n : a.nprob), dim3(block), args, (size_t)a.lds_bytes, s);
     return e != hipSuccess ? e : hipGetLastError();
 }
 

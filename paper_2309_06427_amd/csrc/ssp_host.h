@@ -2,6 +2,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <atomic>
 #include <stdint.h>
 
 namespace ssp {
@@ -179,6 +181,16 @@ int pcg2_fp64_resident(int nx, int threads, int lds_bytes);
 int pcg2_steps_for(int nx, bool fp32, int threads, int lds_bytes);
 // Workgroup sizes the fused kernel is compiled for (128, 256; 512 under FP64 storage).
 bool pcg2_threads_ok(bool fp32, int threads);
+
+// A number kept for each device, 0 until it is set (function attributes hold on one device; beyond the table nothing is
+// kept).  Two threads that find 0 do the same work twice.
+struct PerDevice {
+    std::atomic<int> v[64];
+    int get(int device) const { return device >= 0 && device < 64 ? v[device].load() : 0; }
+    void set(int device, int x) {
+        if (device >= 0 && device < 64) v[device].store(x);
+    }
+};
 
 // Scaled solve of the problems order[0 .. nprob) (all of state size nx, one
 // of kBuildSizes): one persistent grid of the kernel instance compiled for
