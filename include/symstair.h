@@ -415,9 +415,9 @@ ssp_status ssp_scaled_onchip_horizon(int32_t nx, ssp_precon pc, ssp_precision pr
  * 6, 14 or 26 whose vectors fit a CU's LDS can run with its Oh blocks in
  * registers and L2 and its vectors in LDS instead of streaming them each pass.
  * They are the shortest *count problems of that state size; the others
- * stream, side by side with them (in a captured solve of a batch of one state
- * size all stream then).  Both forms return the same bits.  0 under any other solve;
- * SSP_ERR_ARG for a null count or a state size that the batch does not have,
+ * stream.  Both forms return the same bits.  0 where streaming all of them is
+ * expected to be faster (many short horizons, a few too long ones) and under
+ * any other solve; SSP_ERR_ARG for a null count or a state size that the batch does not have,
  * SSP_ERR_STATE before the first build. */
 ssp_status ssp_scaled_onchip_problems(const ssp_batch *b, int32_t nx, int32_t *count);
 

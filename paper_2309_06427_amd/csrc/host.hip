@@ -290,14 +290,6 @@ ssp::SolveArgs solve_args(const ssp_batch *b, double rel_tol, int32_t max_iter, 
     return a;
 }
 
-// s takes part in a graph capture (or may not be asked)
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-
 // The scaled solve: refinement in FP64 around the float inner solve, or
 // FP64 restarts from the true residual under FP64 storage.
 ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
@@ -325,7 +317,6 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
         SSP_HIP(hipEventRecord(b->gevents[ng], s));
         for (int i = 0; i < ng; ++i) SSP_HIP(hipStreamWaitEvent(b->gstreams[i], b->gevents[ng], 0));
     }
-    bool joins[ssp::kBuildClasses] = {};  // at most one group per compiled state size
     for (int i = 0; i < ng; ++i) {
         const auto &g = b->groups[i];
         ssp::SolveArgs ga = a;
@@ -333,36 +324,15 @@ ssp_status launch_scaled(ssp_batch *b, ssp::SolveArgs a, hipStream_t s) {
         ga.queue = a.queue + 2 * i;
         ga.step_knots = ssp::pcg3_steps_for(g.nx, b->fp32, t, a.lds_bytes, a.poly);
         ga.res_knots = ssp::pcg3_residual_steps(g.nx, b->fp32, a.lds_bytes);
-        int streamed = g.count - chip_count(b, g);
-        // A group with both forms runs them side by side (in turn, the GPU is left to a few long problems and then to the
-        // others).  The streaming workgroups spread over the CUs and an on-chip workgroup needs a whole one, so that grid
-        // leaves a CU for each of them, up to half of all: which of the two is dispatched first does not matter then.
-        // Both streams are forked from the caller's and joined back into it, never into each other: a capture cannot end
-        // when a stream that does not own it has joined one that it forked.  So a capture of a batch of one state size,
-        // whose stream may be such a one and is not forked otherwise, streams the whole group.
-        // Measured, in turn and side by side, ms: nx 26, 16 problems of 400 knots and 480 of 300 8.30 and 5.95, 128 of 400
-        // and 128 of 350 7.26 and 6.03, one of 400 and 1000 of 100 7.02 and 5.90; nx 14, 64 of 800 and 192 of 256 4.23
-        // and 4.05.
-        const bool mixed = streamed > 0 && streamed < g.count;
-        if (mixed && !fork && capturing(s)) streamed = g.count;
-        const bool side = mixed && streamed < g.count;
-        const hipStream_t gs = fork ? b->gstreams[i] : s, cs = side ? g.chip_stream : gs;
-        if (side) {
-            SSP_HIP(hipEventRecord(g.chip_fork, s));
-            SSP_HIP(hipStreamWaitEvent(cs, g.chip_fork, 0));
-        }
+        const int streamed = g.count - chip_count(b, g);
         ga.nprob = streamed;
-        SSP_HIP(ssp::launch_pcg3(ga, b->fp32, t, g.nx, 0, gs));
+        SSP_HIP(ssp::launch_pcg3(ga, b->fp32, t, g.nx, 0, fork ? b->gstreams[i] : s));
         ga.order += streamed;
         ga.queue += 1;
         ga.nprob = g.count - streamed;
         ga.lds_bytes = g.chip_lds;
-        SSP_HIP(ssp::launch_pcg4(ga, g.nx, side ? std::min(streamed, b->cus / 2) : 0, cs));
-        if (side) SSP_HIP(hipEventRecord(g.chip_done, cs));
-        joins[i] = side;
+        SSP_HIP(ssp::launch_pcg4(ga, g.nx, fork ? b->gstreams[i] : s));
     }
-    for (int i = 0; i < ng; ++i)
-        if (joins[i]) SSP_HIP(hipStreamWaitEvent(s, b->groups[i].chip_done, 0));
     if (fork) {
         for (int i = 0; i < ng; ++i) {
             SSP_HIP(hipEventRecord(b->gevents[i], b->gstreams[i]));
@@ -695,15 +665,6 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
         }
         if (rc != SSP_OK) g_last_error = "stream/event creation failed";
     }
-    for (auto &g : b->groups) {
-        if (rc != SSP_OK || g.streamed == 0 || g.streamed == g.count) continue;
-        if (hipStreamCreateWithFlags(&g.chip_stream, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&g.chip_fork, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&g.chip_done, hipEventDisableTiming) != hipSuccess) {
-            rc = SSP_ERR_HIP;
-            g_last_error = "stream/event creation failed";
-        }
-    }
     up(&b->dknot, knot_prob.data(), knot_prob.size());
     up(&b->ditems, items.data(), items.size());
     up(&b->ditemrec, itemrec.data(), itemrec.size());
@@ -764,11 +725,6 @@ ssp_status ssp_batch_destroy(ssp_batch *b) {
             if (kl.second.first) (void)hipFree(kl.second.first);
         for (hipStream_t st : b->gstreams) (void)hipStreamDestroy(st);
         for (hipEvent_t ev : b->gevents) (void)hipEventDestroy(ev);
-        for (auto &g : b->groups) {
-            if (g.chip_stream) (void)hipStreamDestroy(g.chip_stream);
-            if (g.chip_fork) (void)hipEventDestroy(g.chip_fork);
-            if (g.chip_done) (void)hipEventDestroy(g.chip_done);
-        }
         if (b->dgorder) (void)hipFree(b->dgorder);
         for (void *p : {(void *)b->dN, (void *)b->dnx, (void *)b->dnu, (void *)b->dorder, (void *)b->dknot,
                         (void *)b->ditems, (void *)b->ditemrec, (void *)b->dgeneric, (void *)b->dkkt, (void *)b->dkktrec, (void *)b->doff_nn, (void *)b->doff_nu, (void *)b->doff_uu, (void *)b->doff_v,

@@ -1082,7 +1082,7 @@ int64_t pcg4_lds(int nx, int N, bool all_vectors) {
     return -1;
 }
 
-hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s) {
+hipError_t launch_pcg4(const SolveArgs &a, int nx, hipStream_t s) {
     if (a.nprob == 0) return hipSuccess;
     const void *f = pcg4_kernel(nx);
     if (!f) return hipErrorInvalidValue;
@@ -1102,7 +1102,7 @@ hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s) {
     }
     // workgroups that fit a CU together: by registers (two waves per SIMD) and LDS
     const int by_lds = 160 * 1024 / (a.lds_bytes + 256), by_reg = 512 / block;
-    n = (n > spare ? n - spare : 1) * (by_lds < by_reg ? by_lds : by_reg);
+    n *= by_lds < by_reg ? by_lds : by_reg;
     SolveArgs arg = a;
     void *args[] = {(void *)&arg};
     e = hipLaunchKernel(f, dim3(n < a.nprob ? n : a.nprob), dim3(block), args, (size_t)a.lds_bytes, s);

@@ -44,9 +44,11 @@ constexpr ScaledCost kScaledCost[] = {{6, 40, 160, 1, 73, 0.67, 1.05, 23, 29, 0.
 // of 64 4092 and 6572; 512 of 8 225 and 197; nx 6, 256 of 32 113 and 100, of 64 129 and 160; 512 of 128 321 and 286;
 // 640 of 32 to 256 428 and 449, 1365 781 and 513.
 //
-// `too_long` leading problems stream in any case.  Beside them the on-chip grid has the CUs that they leave, or waits for
-// them: 256 problems of 400 and 256 of 300 knots at nx 26 take 7.96 ms so and 6.78 when all stream, 600 of 400 and 600
-// of 200 take 10.4 and 11.2.
+// `too_long` leading problems stream in any case, and the on-chip grid follows them on the group's stream, so a few of
+// them would hold up all others: 16 problems of 400 knots before 480 of 300 at nx 26 take 8.2 ms, 256 of 400 before 256 of
+// 300 7.7 and 6.8 when all stream, 600 of 400 before 600 of 200 10.4 and 11.2.  (On a stream of its own the on-chip grid
+// overlaps them, 5.95 ms for the first, but only where the runtime gives the two streams different hardware queues: in a
+// process with many streams it took 8.2 again.)
 bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {
     const ScaledCost *c = nullptr;
     for (const auto &q : kScaledCost)
@@ -62,10 +64,7 @@ bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {
     }
     const double all = schedule(stream, 3 * cus);
     stream.resize(too_long);
-    const double longest = schedule(stream, 3 * cus);
-    double t = longest + schedule(chip, cus);
-    if (too_long < cus) t = std::min(t, std::max(longest, schedule(chip, cus - too_long)));
-    return t <= all;
+    return schedule(stream, 3 * cus) + schedule(chip, cus) <= all;
 }
 
 // A step of the fused pass costs about the same at any state size, 1.07 and 1.6 times as much with 256 and 512 threads

@@ -134,8 +134,6 @@ struct ssp_batch {
         double work = 0;                    // sum of N nx^2 (launch order: largest first)
         int streamed = 0, chip_lds = 0;     // scaled solve under FP32 storage: the first `streamed` problems are too
                                             // long for the on-chip solve, or it does not pay; LDS bytes of the others
-        hipStream_t chip_stream = nullptr;  // of the on-chip problems where the group also has streaming ones, forked
-        hipEvent_t chip_fork = nullptr, chip_done = nullptr;  // from the caller's stream and joined back into it
         int fp64_threads = 128;             // fused solve under FP64 storage without a chosen mapping
         int threads = 0, lds = 0;
         float tuned_ms = 0.0f;  // best solve time the autotuner measured (0: not tuned)

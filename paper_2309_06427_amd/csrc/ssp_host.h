@@ -202,8 +202,7 @@ hipError_t launch_pcg3(const SolveArgs &a, bool fp32, int threads, int nx, int g
 // (with all six vectors there pcg4_lds(nx, N, true); -1: no such state size), at most kLds4Cap.
 constexpr int kLds4Cap = 160 * 1024 - 256;
 int64_t pcg4_lds(int nx, int N, bool all_vectors);
-// `spare`: CUs it leaves to another grid.
-hipError_t launch_pcg4(const SolveArgs &a, int nx, int spare, hipStream_t s);
+hipError_t launch_pcg4(const SolveArgs &a, int nx, hipStream_t s);
 // Whether the problems of state size nx, N[0 .. count) longest first, are faster with all but the first `too_long` on
 // chip than all streaming, on a device of `cus` CUs.
 bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus);

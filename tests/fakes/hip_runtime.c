@@ -30,7 +30,6 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, i
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned f) { (void)f; *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { (void)s; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c) { (void)s; *c = getenv("FAKE_CAPTURE") ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned f) { (void)f; *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { (void)e; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { printf("record %p %p\n", (void *)e, (void *)s); return hipSuccess; }

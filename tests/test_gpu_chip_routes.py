@@ -49,16 +49,23 @@ def assert_same(a, c):
         assert np.array_equal(a[k], c[k], equal_nan=True), k
 
 
-# at, above and below the longest horizon that fits; nx 6 also where p, s and x leave the LDS (from 1065 knots on)
-ENDS = {6: (2129, 2128, 2127, 1070, 1064, 300), 14: (769, 768, 767, 500), 26: (361, 360, 359, 200)}
+# the longest horizon that fits and shorter ones; nx 6 also where p, s and x leave the LDS (from 1065 knots on)
+ENDS = {6: (2128, 2127, 1070, 1064, 300), 14: (768, 767, 500), 26: (360, 359, 200)}
 
 
 @pytest.mark.parametrize("pc", ["sym", "bj", "poly3"])
 @pytest.mark.parametrize("nx", sorted(ENDS))
 def test_horizons_at_the_ends(nx, pc):
     (a, on), (c, off) = both(pack(nx, ENDS[nx]), pc)
-    assert on == {nx: len(ENDS[nx]) - 1} and off == {nx: 0}
+    assert on == {nx: len(ENDS[nx])} and off == {nx: 0}
     assert ((a["status"] & ~16) == 0).all()
+    assert_same(a, c)
+
+
+@pytest.mark.parametrize("nx", sorted(ENDS))
+def test_few_problems_stream_beside_one_that_is_too_long(nx):
+    (a, on), (c, _) = both(pack(nx, (ENDS[nx][0] + 1,) + ENDS[nx]))
+    assert on == {nx: 0}
     assert_same(a, c)
 
 
@@ -94,14 +101,15 @@ def test_many_problems_of_state_size_6_stream():
     assert (a["status"] == 0).all()
 
 
-def test_the_edge_batches_have_on_chip_problems():
-    """The comparisons of test_gpu_chip_solve: every problem below the limits runs on chip in their default arm."""
-    from paper_2309_06427_amd import solver
+@pytest.mark.parametrize("pc", ["bj", "add", "sym", "poly2", "poly3"])
+@pytest.mark.parametrize("nx", sorted(ENDS))
+def test_the_edge_batches_are_on_chip(nx, pc):
+    """The horizons of test_gpu_chip_solve that fit, known to run on chip in one arm and to stream in the other."""
     from .test_gpu_chip_solve import EDGES
-    for nx, ns in EDGES.items():
-        with solver.DeviceBatch(pack(nx, ns)) as db:
-            db.build("sym", "fp32_refine64")
-            assert db.solver.onchip_problems(nx) == sum(n <= ENDS[nx][1] for n in ns)
+    ns = [n for n in EDGES[nx] if n <= ENDS[nx][0]]
+    (a, on), (c, off) = both(pack(nx, ns, 100 + nx), pc)
+    assert on == {nx: len(ns)} and off == {nx: 0}
+    assert_same(a, c)
 
 
 @pytest.mark.parametrize("nx", [14, 26])

@@ -21,7 +21,7 @@ from paper_2309_06427_amd import _lib
 L = _lib.load()
 mem = 4096  # no pointer is followed
 stream = 0x5000
-for dev, sizes, prec, pc in eval(sys.argv[3]):
+for dev, sizes, prec, pc in eval(sys.stdin.read()):
     N, nx = (np.array(v, dtype=np.int32) for v in zip(*sizes))
     p = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))
     h = C.c_void_p()
@@ -45,10 +45,10 @@ def fake(tmp_path_factory):
     return so
 
 
-def calls(fake, work, **env):
+def calls(fake, work):
     """The calls of each solve and, first, all calls in order, as lists of words."""
-    r = subprocess.run([sys.executable, "-c", CHILD, fake, os.path.dirname(HERE), repr(work)], capture_output=True,
-                       text=True, env={**os.environ, **env})
+    r = subprocess.run([sys.executable, "-c", CHILD, fake, os.path.dirname(HERE)], input=repr(work),
+                       capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     lines = [l.split() for l in r.stdout.splitlines()]
     solves, cur = [], None
@@ -81,15 +81,13 @@ def test_large_lds_is_allowed_on_each_device(fake):
     assert large >= 8
 
 
-@pytest.mark.parametrize("sizes", [[(400, 26), (300, 26), (30, 26)],
-                                   [(400, 26), (300, 26), (800, 14), (700, 14), (90, 6), (30, 36)]])
-def test_internal_streams_fork_from_and_join_into_the_callers(fake, sizes):
+def test_internal_streams_fork_from_and_join_into_the_callers(fake):
     """Internal streams wait for events of the caller's stream alone and only the caller's stream waits for theirs (a
     capture cannot end where they join each other); each that launches is joined after its last launch."""
-    _, (calls_,) = calls(fake, [(0, sizes, REFINE, SYM)])
+    _, (calls_,) = calls(fake, [(0, [(400, 26), (30, 26), (700, 14), (90, 6), (30, 36)], REFINE, SYM)])
     caller, recorded, open_ = "0x5000", {}, set()
     launches = [w[4] for w in calls_ if w[0] == "launch"]
-    assert len(set(launches)) >= 2
+    assert len(set(launches)) == 5
     for w in calls_:
         if w[0] == "record":
             recorded[w[1]] = w[2]
@@ -105,7 +103,10 @@ def test_internal_streams_fork_from_and_join_into_the_callers(fake, sizes):
     assert set(launches) - {caller} <= waited
 
 
-def test_captured_solve_of_one_state_size_stays_on_its_stream(fake):
-    _, (calls_,) = calls(fake, [(0, [(400, 26), (300, 26), (30, 26)], REFINE, SYM)], FAKE_CAPTURE="1")
-    assert {w[0] for w in calls_} <= {"launch", "allow"}
-    assert {w[4] for w in calls_ if w[0] == "launch"} == {"0x5000"}
+def test_one_state_size_stays_on_the_callers_stream(fake):
+    """Long problems and, where that pays, the others on chip after them: one stream, both kernels, all problems."""
+    for sizes, blocks in (([(400, 26), (300, 26), (30, 26)], [256]), ([(769, 14)] + [(100, 14)] * 18000, [256, 512])):
+        _, (calls_,) = calls(fake, [(0, sizes, REFINE, SYM)])
+        assert {w[0] for w in calls_} <= {"launch", "allow"}
+        solves = [w for w in calls_ if w[0] == "launch" and int(w[3]) > 0]
+        assert [int(w[6]) for w in solves] == blocks and {w[4] for w in solves} == {"0x5000"}

@@ -53,12 +53,16 @@ def test_scaled_form_is_the_faster_one(nx, n, P, chip, stream):
         assert not pays
 
 
-def test_scaled_form_beside_problems_that_are_too_long():
-    """nx 26: 256 of 400 knots and 256 of 300 (7.96 ms with the latter on chip, 6.78 all streaming); 600 of 400 and 600
-    of 200 (10.4 and 11.2); 16 of 400 and 480 of 300 (5.95 and 8.3 in turn); all of them too long."""
+def test_scaled_form_with_problems_that_are_too_long():
+    """nx 26, the rest on chip after the long ones and all streaming, ms: 256 of 400 knots and 256 of 300 7.72 and 6.84,
+    one of 400 and 1000 of 100 7.02 and 6.14, 600 of 400 and 600 of 200 10.41 and 11.26; nx 14, one of 800 and 1000 of
+    100 4.07 and 3.81.  All of them too long: streaming."""
     assert not chip_pays(26, [400] * 256 + [300] * 256, 256)
+    assert not chip_pays(26, [400] * 16 + [300] * 480, 16)
+    assert not chip_pays(26, [400] + [100] * 1000, 1)
+    assert not chip_pays(14, [800] + [100] * 1000, 1)
     assert chip_pays(26, [400] * 600 + [200] * 600, 600)
-    assert chip_pays(26, [400] * 16 + [300] * 480, 16)
+    assert chip_pays(26, [400] + [100] * 12000, 1)
     assert not chip_pays(26, [400] * 16, 16)
 
 
