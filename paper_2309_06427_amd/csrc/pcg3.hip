@@ -143,22 +143,65 @@ struct Prefetch3 {
         static_for<0, kPF>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             const int q = threadIdx.x + m * BLOCK;
-            if constexpr (lane_major<TM, NX>()) {
-                // the stored order back to rows: the two halves of a vector are pairs of row entries
-                const int kk = q / (BS / V), e = q - kk * (BS / V);
-                int off = base + kk * BS;
-                if (off >= wrap) off -= wrap;
-                const f32x2 lo = {reg[m].x, reg[m].y}, hi = {reg[m].z, reg[m].w};
-                *(f32x2 *)(q < nvec ? ring + off + lane_major_source<NX>(4 * e) : dummy) = lo;
-                *(f32x2 *)(q < nvec ? ring + off + lane_major_source<NX>(4 * e + 2) : dummy) = hi;
-            } else {
-                int off = base + q * V;
-                if (off >= wrap) off -= wrap;
-                *(VT *)(q < nvec ? ring + off : dummy) = reg[m];
-            }
+            int off = base + q * V;
+            if (off >= wrap) off -= wrap;
+            *(VT *)(q < nvec ? ring + off : dummy) = reg[m];
         });
     }
 };
+
+// Row i (COL: column i) of a block of Oh as stored times x: even and odd terms apart, in order.
+template <typename TM, int NX, bool COL>
+__device__ __forceinline__ TM oh_dot(const TM *__restrict__ blk, int i, const TM *__restrict__ x) {
+    if constexpr (!lane_major<TM, NX>()) {
+        return lean_dot<NX, COL>(blk, i, x);
+    } else {
+        // The lane-major order, read as it lies in the ring.  A pass is bound by the latency of its steps and its LDS
+        // accesses: with the rows put back in order at the store (two 8-byte writes for each 16-byte load) 256 problems of
+        // 350 to 400 knots took 6.00 ms, so they take 5.18 (5.81 with blocks stored by rows); 1365 of 32 to 256 5.20,
+        // 5.02 (5.05).
+        constexpr int H = NX / 2, T = 4 * H;
+        TM s0 = TM(0), s1 = TM(0);
+        if constexpr (COL) {
+            // entries (r, i) and (r + H, i), r < H: 4 r past these two
+            const TM *top = blk + lane_major_place<NX>(0, i), *low = blk + lane_major_place<NX>(H, i);
+#pragma unroll 3
+            for (int j = 0; j + 2 < H; j += 2) {
+                const f32x2 v = *(const f32x2 *)(x + j);
+                s0 += top[4 * j] * v.x;
+                s1 += top[4 * j + 4] * v.y;
+            }
+            {
+                const f32x2 v = *(const f32x2 *)(x + H - 1);
+                s0 += top[4 * H - 4] * v.x;
+                s1 += low[0] * v.y;
+            }
+#pragma unroll 3
+            for (int j = 1; j + 1 < H; j += 2) {
+                const f32x2 v = *(const f32x2 *)(x + H + j);
+                s0 += low[4 * j] * v.x;
+                s1 += low[4 * j + 4] * v.y;
+            }
+        } else {
+            // entries (i, 4 t), (i, 4 t + 1) and (i, 4 t + 2), (i, 4 t + 3): T t past these two
+            const TM *a = blk + lane_major_place<NX>(i, 0), *b = blk + lane_major_place<NX>(i, 2);
+#pragma unroll 2
+            for (int t = 0; t < NX / 4; ++t) {
+                const f32x2 v = *(const f32x2 *)(x + 4 * t), w = *(const f32x2 *)(x + 4 * t + 2);
+                const f32x2 c = *(const f32x2 *)(a + T * t), d = *(const f32x2 *)(b + T * t);
+                s0 += c.x * v.x;
+                s1 += c.y * v.y;
+                s0 += d.x * w.x;
+                s1 += d.y * w.y;
+            }
+            static_assert(NX % 4 == 2, "one pair more");
+            const f32x2 v = *(const f32x2 *)(x + NX - 2), c = *(const f32x2 *)(a + T * (NX / 4));
+            s0 += c.x * v.x;
+            s1 += c.y * v.y;
+        }
+        return s0 + s1;
+    }
+}
 
 // Workgroup sums of a pass's partial inner products (fixed-order trees; in
 // FP64 under the FP64-accumulation option, then rounded to the storage type).
@@ -255,10 +298,10 @@ __device__ __forceinline__ Dots3<TI> scaled_pass(const Geo3 &g, bool init, bool 
                 const int k = lo + kk, dk = k - k0;
                 const int s = slot_of(sb, dk, R);
                 TI t = TI(0);
-                if (k > 0) t += lean_dot<NX, false>(ring + s * BS, i, hin + slot_of(sb, dk - 1, R) * NXP);
+                if (k > 0) t += oh_dot<TI, NX, false>(ring + s * BS, i, hin + slot_of(sb, dk - 1, R) * NXP);
                 if (k + 1 < N) {
                     const int sp = slot_of(sb, dk + 1, R);
-                    t += lean_dot<NX, true>(ring + sp * BS, i, hin + sp * NXP);
+                    t += oh_dot<TI, NX, true>(ring + sp * BS, i, hin + sp * NXP);
                 }
                 const TI rk = win[s * NXP + i];
                 const TI h = rk - cc * t;
@@ -284,10 +327,10 @@ __device__ __forceinline__ Dots3<TI> scaled_pass(const Geo3 &g, bool init, bool 
                 const int s = slot_of(sb, dk, R);
                 const TI uk = u[s * NXP + i];
                 TI w = uk;
-                if (k > 0) w += lean_dot<NX, false>(ring + s * BS, i, u + slot_of(sb, dk - 1, R) * NXP);
+                if (k > 0) w += oh_dot<TI, NX, false>(ring + s * BS, i, u + slot_of(sb, dk - 1, R) * NXP);
                 if (k + 1 < N) {
                     const int sp = slot_of(sb, dk + 1, R);
-                    w += lean_dot<NX, true>(ring + sp * BS, i, u + sp * NXP);
+                    w += oh_dot<TI, NX, true>(ring + sp * BS, i, u + sp * NXP);
                 }
                 if (g.acc64)
                     d.d64 += (double)(w * uk);

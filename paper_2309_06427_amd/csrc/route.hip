@@ -40,13 +40,13 @@ constexpr ScaledCost kScaledCost[] = {{6, 40, 160, 1, 73, 0.67, 1.05, 23, 29, 0.
 // The lines were fitted to 633 measured pairs (symmetric stair, block-Jacobi and degree 3 at nx 6, 14, 26; 1 to 768
 // knots, uniform and ragged; 16 to 4096 problems): the form they choose is at most 5% slower than streaming and 14%
 // slower than the better one at any of them.  On chip and streaming, us: nx 14, 4096 problems of 16 knots 1166 and 625,
-// of 32 1299 and 1239, of 64 1712 and 2275; 256 of 16 104 and 128; nx 26, 4096 of 8 1454 and 909, of 16 1695 and 1873,
-// of 64 4092 and 6572; 512 of 8 225 and 197; nx 6, 256 of 32 113 and 100, of 64 129 and 160; 512 of 128 321 and 286;
+// of 32 1299 and 1239, of 64 1712 and 2275; 256 of 16 104 and 128; nx 26, 4096 of 8 1454 and 872, of 16 1700 and 1730;
+// 2048 of 64 2097 and 3200; 512 of 8 225 and 186; nx 6, 256 of 32 113 and 100, of 64 129 and 160; 512 of 128 321 and 286;
 // 640 of 32 to 256 428 and 449, 1365 781 and 513.
 //
 // `too_long` leading problems stream in any case, and the on-chip grid follows them on the group's stream, so a few of
 // them would hold up all others: 16 problems of 400 knots before 480 of 300 at nx 26 take 8.2 ms, 256 of 400 before 256 of
-// 300 7.7 and 6.8 when all stream, 600 of 400 before 600 of 200 10.4 and 11.2.  (On a stream of its own the on-chip grid
+// 300 7.7 and 6.2 when all stream, 600 of 400 before 600 of 200 10.2 and 10.4.  (On a stream of its own the on-chip grid
 // overlaps them, 5.95 ms for the first, but only where the runtime gives the two streams different hardware queues: in a
 // process with many streams it took 8.2 again.)
 bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {

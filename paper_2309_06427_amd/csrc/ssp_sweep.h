@@ -36,13 +36,7 @@ __host__ __device__ inline int knot_stride(int nx, int elem_bytes) {
 constexpr int kLaneMajorNx = 26;
 template <typename TM, int NX>
 constexpr bool lane_major() { return sizeof(TM) == 4 && NX == kLaneMajorNx; }
-// row-major position of the entry stored at e, and back
-template <int NX>
-__host__ __device__ constexpr int lane_major_source(int e) {
-    constexpr int P = NX / 2;
-    const int v = e >> 2, t = v / P, p = v - t * P, f = 4 * t + (e & 3);  // entry f of row pair p
-    return f < NX ? p * NX + f : (p + P) * NX + f - NX;
-}
+// where entry (row, col) is stored
 template <int NX>
 __host__ __device__ constexpr int lane_major_place(int row, int col) {
     constexpr int P = NX / 2;

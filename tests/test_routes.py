@@ -19,11 +19,11 @@ SCALED = [
     (14, 64, 4096, 1.7121, 2.2748), (14, 128, 512, 0.3256, 0.7541), (14, 256, 1024, 1.3694, 2.9087),
     (14, 768, 16, 0.9976, 3.7127), (14, (1, 9), 100, 0.0937, 0.1082), (14, (1, 9), 4096, 0.8539, 0.3831),
     (14, (1, 32), 1365, 0.3964, 0.2944), (14, (1, 32), 300, 0.1439, 0.2046), (14, (32, 256), 4096, 2.9338, 4.5994),
-    (26, 1, 128, 0.0368, 0.0282), (26, 1, 4096, 0.3699, 0.1281), (26, 2, 512, 0.1231, 0.0886), (26, 4, 16, 0.0849, 0.1095),
-    (26, 4, 4096, 1.2211, 0.6930), (26, 8, 256, 0.1247, 0.1743), (26, 8, 512, 0.2248, 0.1968), (26, 8, 4096, 1.4439, 0.9058),
-    (26, 16, 512, 0.2483, 0.3746), (26, 24, 4096, 2.1505, 2.6313), (26, 64, 1024, 1.0995, 2.2059),
-    (26, 360, 256, 1.9299, 5.5498), (26, (1, 12), 4096, 1.2739, 0.8661), (26, (1, 40), 300, 0.2053, 0.6173),
-    (26, (32, 256), 1365, 3.3381, 5.2636),
+    (26, 1, 128, 0.0368, 0.0282), (26, 1, 4096, 0.3699, 0.1301), (26, 2, 512, 0.1231, 0.0828), (26, 4, 16, 0.0849, 0.0995),
+    (26, 4, 4096, 1.2211, 0.6476), (26, 8, 256, 0.1247, 0.1608), (26, 8, 512, 0.2248, 0.1860), (26, 8, 4096, 1.4439, 0.8718),
+    (26, 16, 512, 0.2483, 0.3407), (26, 24, 4096, 2.1505, 2.4373), (26, 64, 1024, 1.0995, 1.9952),
+    (26, 360, 256, 1.9299, 5.5498), (26, (1, 12), 4096, 1.2739, 0.8103), (26, (1, 40), 300, 0.2053, 0.5491),
+    (26, (32, 256), 1365, 3.3381, 5.0505),
     (6, 1, 16, 0.0279, 0.0222), (6, 8, 640, 0.1996, 0.0863), (6, 32, 16, 0.0963, 0.0860), (6, 32, 256, 0.1130, 0.1000),
     (6, 64, 256, 0.1288, 0.1594), (6, 64, 512, 0.2355, 0.1727), (6, 128, 256, 0.1769, 0.2715), (6, 128, 512, 0.3212, 0.2860),
     (6, 256, 256, 0.3025, 0.4533), (6, 256, 640, 0.7361, 0.5370), (6, 985, 64, 0.966, 1.343), (6, 985, 512, 2.245, 1.599),
@@ -54,8 +54,8 @@ def test_scaled_form_is_the_faster_one(nx, n, P, chip, stream):
 
 
 def test_scaled_form_with_problems_that_are_too_long():
-    """nx 26, the rest on chip after the long ones and all streaming, ms: 256 of 400 knots and 256 of 300 7.72 and 6.84,
-    one of 400 and 1000 of 100 7.02 and 6.14, 600 of 400 and 600 of 200 10.41 and 11.26; nx 14, one of 800 and 1000 of
+    """nx 26, the rest on chip after the long ones and all streaming, ms: 256 of 400 knots and 256 of 300 7.72 and 6.23,
+    one of 400 and 1000 of 100 7.02 and 5.47, 600 of 400 and 600 of 200 10.16 and 10.43; nx 14, one of 800 and 1000 of
     100 4.07 and 3.81.  All of them too long: streaming."""
     assert not chip_pays(26, [400] * 256 + [300] * 256, 256)
     assert not chip_pays(26, [400] * 16 + [300] * 480, 16)
