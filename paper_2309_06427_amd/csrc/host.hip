@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <numeric>
 #include <string>
@@ -139,12 +140,28 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
 }
 
 
+// Workgroup size of the FP64 fused solve for a group without a chosen mapping, found when it is first asked for (the
+// current device is the handle's).
+int fp64_threads(const ssp_batch *b, const ssp_batch::Group &g) {
+    if (g.fp64_threads == 0) {
+        std::vector<int32_t> horizons;
+        for (int p = 0; p < b->P; ++p)
+            if (b->nx[p] == g.nx) horizons.push_back(b->N[p]);
+        std::sort(horizons.begin(), horizons.end(), std::greater<int32_t>());
+        int32_t resident[3];
+        for (int q = 0; q < 3; ++q)
+            resident[q] = ssp::pcg2_fp64_resident(g.nx, 128 << q, ssp::pcg2_lds(g.nx, false, 128 << q));
+        g.fp64_threads = ssp::fused_fp64_threads(g.nx, horizons.data(), g.count, b->cus, resident);
+    }
+    return g.fp64_threads;
+}
+
 // Workgroup size and LDS bytes of the fused kernel for one solve group, or
 // lds = 0 if its knots do not fit the fused kernel's registers or LDS.
 void group_mapping(const ssp_batch *b, const ssp_batch::Group &g, int *threads, int *lds) {
     const bool own = g.threads > 0 && ssp::pcg2_threads_ok(b->fp32, g.threads);  // 512 threads are for FP64 storage
     int t = own ? g.threads : b->threads;
-    if (!own && !b->mapping_set && !b->fp32) t = g.fp64_threads;
+    if (!own && !b->mapping_set && !b->fp32) t = fp64_threads(b, g);
     *threads = t;
     *lds = 0;
     // 512 threads given for the whole handle select the explicit kernel
@@ -624,12 +641,6 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
     }
 
     DevGuard g(device);
-    for (auto &gr : b->groups) {
-        int32_t resident[3];
-        for (int q = 0; q < 3; ++q)
-            resident[q] = ssp::pcg2_fp64_resident(gr.nx, 128 << q, ssp::pcg2_lds(gr.nx, false, 128 << q));
-        gr.fp64_threads = ssp::fused_fp64_threads(gr.nx, horizons.data() + gr.offset, gr.count, b->cus, resident);
-    }
     ssp_status rc = SSP_OK;
     auto up = [&](auto **dst, const auto *src, size_t cnt) {
         if (rc != SSP_OK) return;
@@ -1008,9 +1019,9 @@ ssp_status ssp_autotune(ssp_batch *b, double rel_tol, const double *gamma, doubl
     if (!b || !gamma || !lambda || !iters || !relres || !prob_status || !(rel_tol >= 0.0)) return SSP_ERR_ARG;
     if (!b->built) return SSP_ERR_STATE;
     if (b->scaled) return autotune_scaled(b, rel_tol, gamma, lambda, iters, relres, prob_status, stream);
+    DevGuard dg(b->device);
     if (b->kernel == 1 || !fused_ok(b) || use_coop(b))  // only the batched fused kernel has a mapping to tune
         return ssp_solve(b, rel_tol, 0, gamma, lambda, 0, iters, relres, prob_status, stream);
-    DevGuard dg(b->device);
     hipStream_t s = (hipStream_t)stream;
     int32_t *st0 = nullptr;
     if (dalloc(&st0, (size_t)b->P) != hipSuccess) {
@@ -1094,6 +1105,7 @@ ssp_status ssp_set_group_mapping(ssp_batch *b, int32_t nx, int32_t threads, int3
 ssp_status ssp_get_mapping(const ssp_batch *b, int32_t max_groups, int32_t *nx, int32_t *threads,
                            int32_t *lds_bytes, float *tuned_ms, int32_t *ngroups) {
     if (!b || !ngroups || max_groups < 0) return SSP_ERR_ARG;
+    DevGuard dg(b->device);
     const int ng = (int)b->groups.size();
     *ngroups = ng;
     for (int i = 0; i < ng && i < max_groups; ++i) {

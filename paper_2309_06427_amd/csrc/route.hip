@@ -11,18 +11,31 @@ namespace ssp {
 
 namespace {
 
-// End of the last job when jobs of these costs, longest first, each go to the machine that is free first.
-double schedule(const std::vector<double> &cost, int machines) {
-    std::vector<double> end(cost.begin(), cost.begin() + std::min<size_t>(cost.size(), machines));
-    if (end.empty()) return 0.0;
-    std::make_heap(end.begin(), end.end(), std::greater<double>());  // the machine that is free first on top
-    for (size_t j = end.size(); j < cost.size(); ++j) {
-        std::pop_heap(end.begin(), end.end(), std::greater<double>());
-        end.back() += cost[j];
-        std::push_heap(end.begin(), end.end(), std::greater<double>());
+// Jobs of these costs, longest first, each on the machine that is free first: when the last one ends, and bounds of that
+// which need no walk over the jobs.
+struct Schedule {
+    std::vector<double> cost;
+    int machines;
+    double sum = 0.0;
+    explicit Schedule(int m) : machines(std::max(m, 1)) {}
+    void add(double c) {
+        cost.push_back(c);
+        sum += c;
     }
-    return *std::max_element(end.begin(), end.end());
-}
+    double least() const { return cost.empty() ? 0.0 : std::max(cost[0], sum / machines); }
+    double most() const { return cost.empty() ? 0.0 : cost[0] + sum / machines; }
+    double end() const {
+        std::vector<double> free(cost.begin(), cost.begin() + std::min<size_t>(cost.size(), machines));
+        if (free.empty()) return 0.0;
+        std::make_heap(free.begin(), free.end(), std::greater<double>());  // the machine that is free first on top
+        for (size_t j = free.size(); j < cost.size(); ++j) {
+            std::pop_heap(free.begin(), free.end(), std::greater<double>());
+            free.back() += cost[j];
+            std::push_heap(free.begin(), free.end(), std::greater<double>());
+        }
+        return *std::max_element(free.begin(), free.end());
+    }
+};
 
 // One problem of N knots in microseconds.  On chip, a workgroup per CU: a start, then a solve that grows with the knots,
 // faster past the `held` ones in registers.  Streaming, three workgroups per CU: a solve that grows with the steps of
@@ -54,17 +67,21 @@ bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {
     for (const auto &q : kScaledCost)
         if (q.nx == nx) c = &q;
     if (!c || too_long >= count) return false;
-    std::vector<double> chip, stream;
+    Schedule chip(cus), all(3 * cus), longest(3 * cus);
     for (int j = 0; j < count; ++j) {
         const double n = N[j], early = std::min(n, 5.0) / 5.0;
-        stream.push_back(early * (c->stream + c->stream_step * ((N[j] + (int64_t)c->step - 1) / c->step) + c->stream_knot * n));
-        if (j >= too_long)
-            chip.push_back(c->chip0 + early * (c->chip + c->chip_knot * std::min<double>(n, c->held) +
-                                               c->chip_more * std::max<double>(n - c->held, 0)));
+        const double stream =
+            early * (c->stream + c->stream_step * ((N[j] + (int64_t)c->step - 1) / c->step) + c->stream_knot * n);
+        all.add(stream);
+        if (j < too_long)
+            longest.add(stream);
+        else
+            chip.add(c->chip0 + early * (c->chip + c->chip_knot * std::min<double>(n, c->held) +
+                                         c->chip_more * std::max<double>(n - c->held, 0)));
     }
-    const double all = schedule(stream, 3 * cus);
-    stream.resize(too_long);
-    return schedule(stream, 3 * cus) + schedule(chip, cus) <= all;
+    if (longest.most() + chip.most() <= all.least()) return true;
+    if (longest.least() + chip.least() > all.most()) return false;
+    return longest.end() + chip.end() <= all.end();
 }
 
 // A step of the fused pass costs about the same at any state size, 1.07 and 1.6 times as much with 256 and 512 threads
@@ -79,10 +96,11 @@ int fused_fp64_threads(int nx, const int32_t *N, int count, int cus, const int32
     for (int t : {128, 256, 512}) {
         const int lds = pcg2_lds(nx, false, t), knots = lds ? pcg2_steps_for(nx, false, t, lds) : 0;
         if (knots < 1) continue;
-        std::vector<double> cost;
+        Schedule q(cus * std::max(resident[t >> 8], 1));
         for (int j = 0; j < count; ++j)
-            cost.push_back((t == 128 ? 1.0 : t == 256 ? 1.07 : 1.6) * ((N[j] + (int64_t)knots - 1) / knots));
-        const double end = schedule(cost, cus * std::max(resident[t >> 8], 1));
+            q.add((t == 128 ? 1.0 : t == 256 ? 1.07 : 1.6) * ((N[j] + (int64_t)knots - 1) / knots));
+        if (shortest > 0.0 && q.least() >= shortest) continue;
+        const double end = q.end();
         if (shortest == 0.0 || end < shortest) {
             shortest = end;
             best = t;

@@ -134,7 +134,7 @@ struct ssp_batch {
         double work = 0;                    // sum of N nx^2 (launch order: largest first)
         int streamed = 0, chip_lds = 0;     // scaled solve under FP32 storage: the first `streamed` problems are too
                                             // long for the on-chip solve, or it does not pay; LDS bytes of the others
-        int fp64_threads = 128;             // fused solve under FP64 storage without a chosen mapping
+        mutable int fp64_threads = 0;       // fused solve under FP64 storage without a chosen mapping (0: not known yet)
         int threads = 0, lds = 0;
         float tuned_ms = 0.0f;  // best solve time the autotuner measured (0: not tuned)
     };
