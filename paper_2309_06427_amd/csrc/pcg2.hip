@@ -82,7 +82,8 @@ __host__ __device__ inline int pcg2_knots_per_step(int nx, int block, int lds_by
 // loads) and the six recurrence vectors of this thread's lead row.  Every
 // load is issued unconditionally (surplus slots re-read the step's first
 // vector), so the compiler can count outstanding loads and the compute
-// phases never wait on them.  The loads go out in kParts parts between the
+// phases never wait on them.  With 512 threads, and where the state size is not
+// compiled in, the loads go out in kParts parts between the
 // phases of the current step: issued at once they fill the memory pipeline,
 // and every wave stands there while nothing is computed.  Their addresses are
 // formed where they are used: kept from step to step they were spilled, and a
@@ -90,8 +91,13 @@ __host__ __device__ inline int pcg2_knots_per_step(int nx, int block, int lds_by
 // 128 knots from HBM, 512 threads: one pass 330 thousand cycles before, 255
 // now, of which 20 to 60 in each of store, B, C, D and E, bound by the LDS
 // reads of 7 matrix and 7 vector terms a row; FP64 solve of 1024 problems of
-// condition 1e6: 69.1 ms before, 59.4 now.)
-template <typename TM, int BLOCK>
+// condition 1e6: 69.1 ms before, 59.4 now; FP32, 300 problems of 60 knots of
+// nx 20 2.93 ms at once, 2.67 in parts.)  The smaller workgroups of compiled
+// sizes, whose steps are shorter than the loads, issue them at once, as early as
+// they can, and keep the addresses: 600 problems of 144 knots, scalar Jacobi
+// under FP32 in parts and at once 4.14 and 3.21 ms at nx 14, 15.6 and 12.2 at
+// 26, 39.1 and 26.9 at 36; FP64 with 256 threads 21.6 and 18.4 at nx 26.
+template <typename TM, int BLOCK, int NX>
 struct Prefetch {
     using VT = typename Vec16<TM>::T;
     static constexpr int V = Vec16<TM>::V;
@@ -100,17 +106,19 @@ struct Prefetch {
     TM vec[6];       // u, w, p, s, x, r of this thread's lead row
     double res = 0;  // init pass: the FP64 residual of that row instead
 
-    static constexpr int kParts = 4;
+    static constexpr int kParts = loads_in_parts<TM, BLOCK, NX>() ? 4 : 1;
+    static constexpr bool AGAIN = kParts > 1;
 
     // part PART of the loads of the step of kc knots from k0
     template <int PART>
     __device__ __forceinline__ void issue(const TM *B3, int k0, int kc, int ks, bool init, int lead_row,
                                           const double *r64, const Vecs<TM> vs) {
-        constexpr int m0 = PART * kPF / kParts, m1 = (PART + 1) * kPF / kParts;
+        if constexpr (PART >= kParts) return;
+        constexpr int m0 = PART * kPF / kParts, m1 = PART < kParts ? (PART + 1) * kPF / kParts : m0;
         // the step's D, L, D^-1 blocks: one contiguous chunk of kc knot strides
         const int nvec = kc * ks / V;
         const VT *src = (const VT *)(B3 + (int64_t)k0 * ks);
-        const int t = fresh(threadIdx.x);
+        const int t = fresh_if<AGAIN>(threadIdx.x);
         static_for<m0, m1>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             int q = t + m * BLOCK;
@@ -118,7 +126,7 @@ struct Prefetch {
             reg[m] = src[q];
         });
         if constexpr (PART == 0) {
-            const int row = fresh(lead_row >= 0 ? lead_row : 0);
+            const int row = fresh_if<AGAIN>(lead_row >= 0 ? lead_row : 0);
             if (init) {
                 res = r64[row];
             } else {
@@ -172,6 +180,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
                                                TI *Xv, TI *smem) {
     using TM = TI;
     constexpr int W = BLOCK / 64;
+    constexpr bool PARTS = loads_in_parts<TM, BLOCK, NX>();
     const int nx = NX > 0 ? NX : g.nx, bs = g.bs, bp = g.bp, ks = g.ks, nxp = g.nxp;
     const int N = g.N, C = g.C, R = g.R, RU = g.RU, kw = g.kw;
     TM *ring = smem;  // slot s: D (packed) at s * ks, L at + bp, D^-1 (packed) at + bp + bs
@@ -196,18 +205,28 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
     // s / sp: block-ring slots of k / k + 1
     auto s_row = [&](const TI *xb, int sx, int sxm, int sxp, int s, int sp, bool diag) -> TI {
         TI y = TI(0);
-        const int r = fresh(i);
+        const int r = fresh_if<PARTS>(i);
         if (diag) y += sym_dot<NX>(rD + s * ss, r, xb + sx * nxp, nx);        // D_k (packed)
         if (sxm >= 0) y += row_dot<NX>(rL + s * ss, r, xb + sxm * nxp, nx);   // row i of L_k
         if (sxp >= 0) y += col_dot<NX>(rL + sp * ss, r, xb + sxp * nxp, nx);  // column i of L_{k+1}
         return y;
     };
 
-    // results of the previous step, written at the start of the next one
-    TI oU = TI(0), oW = TI(0);
-    int rowU = -1, rowW = -1;
+    // results of the previous step, written at the start of the next one (those of A at once where the loads go out in parts)
+    TI oP = TI(0), oS = TI(0), oX = TI(0), oR = TI(0), oU = TI(0), oW = TI(0);
+    int rowA = -1, rowU = -1, rowW = -1;
+    auto write_a = [&]() {
+        if (rowA >= 0) {
+            if (!init) {
+                Pv[rowA] = oP;
+                Sv[rowA] = oS;
+            }
+            Xv[rowA] = oX;
+            Rv[rowA] = oR;
+        }
+    };
 
-    Prefetch<TM, BLOCK> pf;
+    Prefetch<TM, BLOCK, NX> pf;
     const int nsteps = (N + C - 1) / C;
     auto lead_row = [&](int k0, int kc) { return (lane_ok && kme < kc) ? (k0 + kme) * nx + i : -1; };
     static_for<0, 4>([&](auto part) {
@@ -219,43 +238,73 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
         const bool last = k1 == N;
         __syncthreads();  // every reader of the slots about to be refilled is done
         pf.store(ring, kc, sb, ks, R, vu + RU * nxp);
-        // the rows that the previous step finished, then A: recurrence updates on the lead rows, written before the
-        // next loads go out
-        if (rowU >= 0) Uv[rowU] = oU;
-        if (rowW >= 0) Wv[rowW] = oW;
-        rowU = rowW = -1;
-        const bool lead = lane_ok && kme < kc;
-        const int sl = slot_of(sb, kme, R);
-        if (lead) {
-            const int row = (k0 + kme) * nx + i;
-            TI r;
-            if (init) {
-                r = (TI)(pf.res * inv_s);
-                Xv[row] = TI(0);
-            } else {
-                const TI pv = first ? pf.vec[0] : pf.vec[0] + beta * pf.vec[2];
-                const TI sv = first ? pf.vec[1] : pf.vec[1] + beta * pf.vec[3];
-                Pv[row] = pv;
-                Sv[row] = sv;
-                Xv[row] = pf.vec[4] + alpha * pv;
-                r = pf.vec[5] - alpha * sv;
-            }
-            Rv[row] = r;
-            vr[sl * nxp + i] = r;
-            d.rho += r * r;
-        }
         auto issue = [&](auto part) {
             if (!last)
                 pf.template issue<decltype(part)::value>(B3, k1, min(C, N - k1), ks, init,
                                                          lead_row(k1, min(C, N - k1)), r64, vsrc);
         };
-        issue(std::integral_constant<int, 0>{});
+        const bool lead = lane_ok && kme < kc;
+        const int sl = slot_of(sb, kme, R);
+        // the rows that the previous step finished, written before the next loads go out, and A: recurrence updates on
+        // the lead rows
+        if constexpr (PARTS) {
+            if (rowU >= 0) Uv[rowU] = oU;
+            if (rowW >= 0) Wv[rowW] = oW;
+            rowU = rowW = -1;
+            if (lead) {
+                const int row = (k0 + kme) * nx + i;
+                TI r;
+                if (init) {
+                    r = (TI)(pf.res * inv_s);
+                    Xv[row] = TI(0);
+                } else {
+                    const TI pv = first ? pf.vec[0] : pf.vec[0] + beta * pf.vec[2];
+                    const TI sv = first ? pf.vec[1] : pf.vec[1] + beta * pf.vec[3];
+                    Pv[row] = pv;
+                    Sv[row] = sv;
+                    Xv[row] = pf.vec[4] + alpha * pv;
+                    r = pf.vec[5] - alpha * sv;
+                }
+                Rv[row] = r;
+                vr[sl * nxp + i] = r;
+                d.rho += r * r;
+            }
+            issue(std::integral_constant<int, 0>{});
+        } else {
+            TM cur[6];
+#pragma unroll
+            for (int v = 0; v < 6; ++v) cur[v] = pf.vec[v];
+            const double res = pf.res;
+            write_a();
+            if (rowU >= 0) Uv[rowU] = oU;
+            if (rowW >= 0) Wv[rowW] = oW;
+            rowA = rowU = rowW = -1;
+            issue(std::integral_constant<int, 0>{});
+            if (lead) {
+                TI r;
+                if (init) {
+                    r = (TI)(res * inv_s);
+                    oX = TI(0);
+                } else {
+                    const TI pv = first ? cur[0] : cur[0] + beta * cur[2];
+                    const TI sv = first ? cur[1] : cur[1] + beta * cur[3];
+                    oP = pv;
+                    oS = sv;
+                    oX = cur[4] + alpha * pv;
+                    r = cur[5] - alpha * sv;
+                }
+                oR = r;
+                rowA = (k0 + kme) * nx + i;
+                vr[sl * nxp + i] = r;
+                d.rho += r * r;
+            }
+        }
         __syncthreads();  // the ring blocks stored above come from every wave
         issue(std::integral_constant<int, 1>{});
         // B: y = D^-1 r on the lead knots (u itself for block-Jacobi)
         if (lead) {
             const TI *rk = vr + sl * nxp;
-            const TI y = sym_dot<NX>(rDi + sl * ss, fresh(i), rk, nx);
+            const TI y = sym_dot<NX>(rDi + sl * ss, fresh_if<PARTS>(i), rk, nx);
             if (bj) {
                 vu[slot_of(sbu, kme, RU) * nxp + i] = y;
                 oU = y;
@@ -285,7 +334,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
                 if (!lane_ok) break;
                 const int k = tlo + kk, dk = k - k0;
                 const int s = slot_of(sb, dk, R);
-                const TI z = sym_dot<NX>(rDi + s * ss, fresh(i), vt + s * nxp, nx);
+                const TI z = sym_dot<NX>(rDi + s * ss, fresh_if<PARTS>(i), vt + s * nxp, nx);
                 const TI u = vy[s * nxp + i] - c2 * z;
                 vu[slot_of(sbu, dk, RU) * nxp + i] = u;
                 d.gam += vr[s * nxp + i] * u;
@@ -326,6 +375,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
         sbu += C;
         if (sbu >= RU) sbu -= RU;
     }
+    if constexpr (!PARTS) write_a();
     if (rowU >= 0) Uv[rowU] = oU;
     if (rowW >= 0) Wv[rowW] = oW;
     return d;

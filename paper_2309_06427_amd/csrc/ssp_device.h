@@ -51,6 +51,13 @@ __device__ __forceinline__ int fresh(int v) {
     return v;
 }
 
+// The same where AGAIN, else the index itself.
+template <bool AGAIN>
+__device__ __forceinline__ int fresh_if(int v) {
+    if constexpr (AGAIN) return fresh(v);
+    return v;
+}
+
 // Butterfly sum over the 64 lanes of a wavefront.  Every lane ends with the
 // same bits: each stage adds the same two operands on both partner lanes.
 // All stages are register moves between lanes (half and quarter swaps, then

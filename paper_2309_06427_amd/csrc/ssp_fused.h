@@ -14,6 +14,11 @@ namespace ssp {
 
 namespace {
 
+// Kernel instances of the fused solve whose next step's loads go out in parts between the phases of a step, at addresses
+// formed anew (see Prefetch in pcg2.hip); NX = 0: any state size.
+template <typename TM, int BLOCK, int NX>
+constexpr bool loads_in_parts() { return NX == 0 || (sizeof(TM) == 8 && BLOCK == 512); }
+
 template <typename TM>
 struct Vec16;
 template <>
@@ -255,7 +260,7 @@ __device__ __forceinline__ ResNorms residual_pass(int N, int C, const TM *__rest
     double lamv = 0.0;
 
     auto issue = [&](int k0, int kc) {
-        const int nvec = kc * VPK, t = fresh(threadIdx.x);
+        const int nvec = kc * VPK, t = fresh_if<loads_in_parts<TM, BLOCK, NX>()>(threadIdx.x);
         static_for<0, KP>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             int q = t + m * BLOCK;
