@@ -398,7 +398,7 @@ ssp_status launch_groups(ssp_batch *b, ssp::SolveArgs a, int which, hipStream_t 
         ssp::SolveArgs ga = a;
         ga.order = b->dgorder + g.offset;
         ga.lds_bytes = l;
-        SSP_HIP(ssp::launch_pcg2(ga, g.count, b->fp32, t, g.nx, fork ? b->gstreams[i] : s));
+        SSP_HIP(ssp::launch_pcg2(ga, g.count, b->fp32, t, g.nx, g.longest, fork ? b->gstreams[i] : s));
     }
     if (fork) {
         for (int i = 0; i < ng; ++i) {
@@ -583,6 +583,7 @@ ssp_status ssp_batch_create(int32_t nprob, const int32_t *N, const int32_t *nx, 
         for (int32_t p : order)
             if (nx[p] == g.nx) gorder.push_back(p);
         g.count = (int)gorder.size() - g.offset;
+        g.longest = N[gorder[g.offset]];
         // the on-chip solve's share: all six vectors in LDS for the longest of its problems where they fit
         auto fits = [&](int32_t p) {
             const int64_t l = ssp::pcg4_lds(g.nx, N[p], false);

@@ -82,22 +82,24 @@ __host__ __device__ inline int pcg2_knots_per_step(int nx, int block, int lds_by
 // loads) and the six recurrence vectors of this thread's lead row.  Every
 // load is issued unconditionally (surplus slots re-read the step's first
 // vector), so the compiler can count outstanding loads and the compute
-// phases never wait on them.  With 512 threads, and where the state size is not
-// compiled in, the loads go out in kParts parts between the
-// phases of the current step: issued at once they fill the memory pipeline,
-// and every wave stands there while nothing is computed.  Their addresses are
-// formed where they are used: kept from step to step they were spilled, and a
-// spilled value's reload waits for the loads issued before it.  (FP64, nx 26,
-// 128 knots from HBM, 512 threads: one pass 330 thousand cycles before, 255
-// now, of which 20 to 60 in each of store, B, C, D and E, bound by the LDS
+// phases never wait on them.  PARTS: the loads go out in kParts parts between
+// the phases of the current step (issued at once they fill the memory pipeline,
+// and every wave stands there while nothing is computed), and their addresses
+// are formed where they are used (kept from step to step they were spilled, and
+// a spilled value's reload waits for the loads issued before it).  FP64, nx 26,
+// 128 knots from HBM, 512 threads: one pass 330 thousand cycles at once, 255 in
+// parts, of which 20 to 60 in each of store, B, C, D and E, bound by the LDS
 // reads of 7 matrix and 7 vector terms a row; FP64 solve of 1024 problems of
-// condition 1e6: 69.1 ms before, 59.4 now; FP32, 300 problems of 60 knots of
-// nx 20 2.93 ms at once, 2.67 in parts.)  The smaller workgroups of compiled
-// sizes, whose steps are shorter than the loads, issue them at once, as early as
-// they can, and keep the addresses: 600 problems of 144 knots, scalar Jacobi
-// under FP32 in parts and at once 4.14 and 3.21 ms at nx 14, 15.6 and 12.2 at
-// 26, 39.1 and 26.9 at 36; FP64 with 256 threads 21.6 and 18.4 at nx 26.
-template <typename TM, int BLOCK, int NX>
+// condition 1e6: 69.1 ms at once, 59.4 in parts; FP32, 300 problems of 60 knots
+// of nx 20 2.93 and 2.67.  Workgroups of 128 and 256 threads with a compiled
+// state size issue them at once, as early as they can: their steps are shorter
+// than the loads.  600 problems of 144 knots, scalar Jacobi under FP32, in parts
+// and at once: nx 14 4.14 and 3.21 ms, 26 15.6 and 12.2, 36 39.1 and 26.9; FP64
+// with 256 threads 21.6 and 18.4 at nx 26.  Only where a problem has up to three
+// steps and the instance spills (nx 26, 36; nx 14 under FP64) the parts are better
+// again, FP64 with 128 threads: nx 14, 4096 problems of 4 knots 0.52 and 0.64 ms,
+// 1024 of 32 1.03 and 0.97; nx 26, 4096 of 2 0.58 and 0.76, of 8 4.86 and 4.65.
+template <typename TM, int BLOCK, bool PARTS>
 struct Prefetch {
     using VT = typename Vec16<TM>::T;
     static constexpr int V = Vec16<TM>::V;
@@ -106,8 +108,7 @@ struct Prefetch {
     TM vec[6];       // u, w, p, s, x, r of this thread's lead row
     double res = 0;  // init pass: the FP64 residual of that row instead
 
-    static constexpr int kParts = loads_in_parts<TM, BLOCK, NX>() ? 4 : 1;
-    static constexpr bool AGAIN = kParts > 1;
+    static constexpr int kParts = PARTS ? 4 : 1;
 
     // part PART of the loads of the step of kc knots from k0
     template <int PART>
@@ -118,7 +119,7 @@ struct Prefetch {
         // the step's D, L, D^-1 blocks: one contiguous chunk of kc knot strides
         const int nvec = kc * ks / V;
         const VT *src = (const VT *)(B3 + (int64_t)k0 * ks);
-        const int t = fresh_if<AGAIN>(threadIdx.x);
+        const int t = fresh_if<PARTS>(threadIdx.x);
         static_for<m0, m1>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             int q = t + m * BLOCK;
@@ -126,7 +127,7 @@ struct Prefetch {
             reg[m] = src[q];
         });
         if constexpr (PART == 0) {
-            const int row = fresh_if<AGAIN>(lead_row >= 0 ? lead_row : 0);
+            const int row = fresh_if<PARTS>(lead_row >= 0 ? lead_row : 0);
             if (init) {
                 res = r64[row];
             } else {
@@ -173,14 +174,13 @@ struct Dots {
 // One fused pass over the knots (see the file comment).  init: the pass that
 // starts an inner solve (r = r64 / ||r64||, x = 0); first: the first update
 // pass (p = u, s = w).
-template <typename TI, int BLOCK, int NX>
+template <typename TI, int BLOCK, int NX, bool PARTS>
 __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init, bool first, TI alpha, TI beta,
                                                double inv_s, const double *__restrict__ r64,
                                                const TI *__restrict__ B3, TI *Rv, TI *Uv, TI *Wv, TI *Pv, TI *Sv,
                                                TI *Xv, TI *smem) {
     using TM = TI;
     constexpr int W = BLOCK / 64;
-    constexpr bool PARTS = loads_in_parts<TM, BLOCK, NX>();
     const int nx = NX > 0 ? NX : g.nx, bs = g.bs, bp = g.bp, ks = g.ks, nxp = g.nxp;
     const int N = g.N, C = g.C, R = g.R, RU = g.RU, kw = g.kw;
     TM *ring = smem;  // slot s: D (packed) at s * ks, L at + bp, D^-1 (packed) at + bp + bs
@@ -226,7 +226,7 @@ __device__ __forceinline__ Dots<TI> fused_pass(const Geo2 &g, int pc, bool init,
         }
     };
 
-    Prefetch<TM, BLOCK, NX> pf;
+    Prefetch<TM, BLOCK, PARTS> pf;
     const int nsteps = (N + C - 1) / C;
     auto lead_row = [&](int k0, int kc) { return (lane_ok && kme < kc) ? (k0 + kme) * nx + i : -1; };
     static_for<0, 4>([&](auto part) {
@@ -403,7 +403,7 @@ struct Outcome {
 
 // FP64 refinement loop around the fused inner PCG, for state size NX
 // (0 = runtime nx).
-template <typename TI, int BLOCK, int NX>
+template <typename TI, int BLOCK, int NX, bool PARTS>
 __device__ __forceinline__ Outcome solve_problem(const SolveArgs &a, const Prob<TI> q, int nx_rt,
                                               unsigned char *smem_raw, double *red64, TI *redT) {
     using TM = TI;
@@ -440,7 +440,7 @@ __device__ __forceinline__ Outcome solve_problem(const SolveArgs &a, const Prob<
             // true residual r = gamma - S lambda in FP64
             ResNorms nr{0.0, 0.0};
             if (NX > 0 && Cres >= 1) {
-                nr = residual_pass<TM, BLOCK, (NX > 0 ? NX : 2)>(N, Cres, q.B3, q.SDlo, q.SLlo, q.lam, q.gam,
+                nr = residual_pass<TM, BLOCK, (NX > 0 ? NX : 2), PARTS>(N, Cres, q.B3, q.SDlo, q.SLlo, q.lam, q.gam,
                                                                  q.r64, (double *)smem_raw);
             } else {
                 bt_sweep<double, TM, BLOCK, NX>(
@@ -502,7 +502,7 @@ __device__ __forceinline__ Outcome solve_problem(const SolveArgs &a, const Prob<
 
         // inner PCG on S d = r / ||r|| from d = 0
         int it = 0, ist = kOk;
-        Dots<TI> dt = fused_pass<TI, BLOCK, NX>(g, pcur, true, false, TI(0), TI(0), inv_s, rsrc, q.B3, q.Rv, q.Uv,
+        Dots<TI> dt = fused_pass<TI, BLOCK, NX, PARTS>(g, pcur, true, false, TI(0), TI(0), inv_s, rsrc, q.B3, q.Rv, q.Uv,
                                                 q.Wv, q.Pv, q.Sv, q.Xv, (TI *)smem_raw);
         block_sum2<BLOCK>(dt.gam, dt.del, redT);
         dt.rho = block_sum<BLOCK>(dt.rho, redT + 2 * (BLOCK / kWave));
@@ -535,7 +535,7 @@ __device__ __forceinline__ Outcome solve_problem(const SolveArgs &a, const Prob<
             }
             alpha = dt.gam / den;
             gam_prev = dt.gam;
-            dt = fused_pass<TI, BLOCK, NX>(g, pcur, false, it == 0, alpha, beta, 0.0, q.r64, q.B3, q.Rv, q.Uv, q.Wv,
+            dt = fused_pass<TI, BLOCK, NX, PARTS>(g, pcur, false, it == 0, alpha, beta, 0.0, q.r64, q.B3, q.Rv, q.Uv, q.Wv,
                                            q.Pv, q.Sv, q.Xv, (TI *)smem_raw);
             block_sum2<BLOCK>(dt.gam, dt.del, redT);
             dt.rho = block_sum<BLOCK>(dt.rho, redT + 2 * (BLOCK / kWave));
@@ -562,7 +562,7 @@ __device__ __forceinline__ Outcome solve_problem(const SolveArgs &a, const Prob<
 
 // One launch per solve group; NX > 0: every problem of the launch has state
 // size NX (compiled in), NX = 0: any state size.
-template <typename TI, int BLOCK, int NX>
+template <typename TI, int BLOCK, int NX, bool PARTS>
 __global__ __launch_bounds__(BLOCK, 2) void k_pcg2(SolveArgs a) {
     using TM = TI;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_pcg2(SolveArgs a) {
     } else if (gg == 0.0) {
         for (int row = tid; row < n; row += BLOCK) q.lam[row] = 0.0;
     } else {
-        o = solve_problem<TI, BLOCK, NX>(a, q, nx, smem_raw, red64, redT);
+        o = solve_problem<TI, BLOCK, NX, PARTS>(a, q, nx, smem_raw, red64, redT);
     }
     if (tid == 0) {
         a.iters[p] = o.total;
@@ -666,7 +666,7 @@ int pcg2_lds(int nx_max, bool fp32, int threads) {
 
 // All the LDS a workgroup may have is allowed once per device; each launch asks for its own size (launches of other sizes
 // may be in flight on other streams).
-template <typename TI, int BLOCK, int NX>
+template <typename TI, int BLOCK, int NX, bool PARTS>
 static hipError_t allow2_t(int *allowed) {
     static PerDevice cap;
     int dev = 0;
@@ -674,7 +674,7 @@ static hipError_t allow2_t(int *allowed) {
     if (e != hipSuccess) return e;
     *allowed = cap.get(dev);
     if (*allowed) return hipSuccess;
-    const void *f = (const void *)k_pcg2<TI, BLOCK, NX>;
+    const void *f = (const void *)k_pcg2<TI, BLOCK, NX, PARTS>;
     hipFuncAttributes fa;
     if ((e = hipFuncGetAttributes(&fa, f)) != hipSuccess) return e;
     *allowed = 160 * 1024 - (int)fa.sharedSizeBytes;
@@ -683,21 +683,22 @@ static hipError_t allow2_t(int *allowed) {
     return hipSuccess;
 }
 
-template <typename TI, int BLOCK, int NX>
+template <typename TI, int BLOCK, int NX, bool PARTS>
 static hipError_t launch2_t(const SolveArgs &a, int nprob, hipStream_t s) {
     int allowed = 0;
-    hipError_t e = allow2_t<TI, BLOCK, NX>(&allowed);
+    hipError_t e = allow2_t<TI, BLOCK, NX, PARTS>(&allowed);
     if (e != hipSuccess) return e;
     if (a.lds_bytes > allowed) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_pcg2<TI, BLOCK, NX>), dim3(nprob), dim3(BLOCK), a.lds_bytes, s, a);
+    hipLaunchKernelGGL((k_pcg2<TI, BLOCK, NX, PARTS>), dim3(nprob), dim3(BLOCK), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 
 template <int BLOCK, int NX>
 static int resident2_t(int lds_bytes) {
+    constexpr bool PARTS = NX != 6 || BLOCK == 512;  // where there are two forms, a CU holds as many of either
     int allowed = 0, n = 0;
-    if (allow2_t<double, BLOCK, NX>(&allowed) != hipSuccess || lds_bytes > allowed) return 0;
-    const void *f = (const void *)k_pcg2<double, BLOCK, NX>;
+    if (allow2_t<double, BLOCK, NX, PARTS>(&allowed) != hipSuccess || lds_bytes > allowed) return 0;
+    const void *f = (const void *)k_pcg2<double, BLOCK, NX, PARTS>;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, BLOCK, (size_t)lds_bytes) == hipSuccess ? n : 0;
 }
 template <int BLOCK>
@@ -719,31 +720,43 @@ int pcg2_fp64_resident(int nx, int threads, int lds_bytes) {
     return 0;
 }
 
+// A state size with a compiled-in specialisation, in the form that the horizons call for (see Prefetch; `few`: no problem
+// has more than three steps).
+template <typename TI, int BLOCK, int NX>
+static hipError_t launch2_c(const SolveArgs &a, int nprob, bool few, hipStream_t s) {
+    constexpr bool spills = NX > 14 || (NX == 14 && sizeof(TI) == 8);
+    if constexpr (BLOCK < 512 && spills) {
+        if (few) return launch2_t<TI, BLOCK, NX, true>(a, nprob, s);
+    }
+    return launch2_t<TI, BLOCK, NX, BLOCK == 512>(a, nprob, s);
+}
 template <typename TI, int BLOCK>
-static hipError_t launch2_nx(const SolveArgs &a, int nprob, int nx, hipStream_t s) {
-    switch (nx) {  // state sizes with a compiled-in specialisation; others use the runtime path
-        case 6: return launch2_t<TI, BLOCK, 6>(a, nprob, s);
-        case 14: return launch2_t<TI, BLOCK, 14>(a, nprob, s);
-        case 26: return launch2_t<TI, BLOCK, 26>(a, nprob, s);
-        case 36: return launch2_t<TI, BLOCK, 36>(a, nprob, s);
-        default: return launch2_t<TI, BLOCK, 0>(a, nprob, s);
+static hipError_t launch2_nx(const SolveArgs &a, int nprob, int nx, int longest, hipStream_t s) {
+    const int knots = pcg2_knots_per_step<TI>(nx, BLOCK, a.lds_bytes);
+    const bool few = knots > 0 && (longest + (int64_t)knots - 1) / knots <= 3;
+    switch (nx) {
+        case 6: return launch2_c<TI, BLOCK, 6>(a, nprob, few, s);
+        case 14: return launch2_c<TI, BLOCK, 14>(a, nprob, few, s);
+        case 26: return launch2_c<TI, BLOCK, 26>(a, nprob, few, s);
+        case 36: return launch2_c<TI, BLOCK, 36>(a, nprob, few, s);
+        default: return launch2_t<TI, BLOCK, 0, true>(a, nprob, s);
     }
 }
 
 bool pcg2_threads_ok(bool fp32, int threads) { return threads == 128 || threads == 256 || (threads == 512 && !fp32); }
 
-hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, int nx, hipStream_t s) {
+hipError_t launch_pcg2(const SolveArgs &a, int nprob, bool fp32, int threads, int nx, int longest, hipStream_t s) {
     if (nprob == 0) return hipSuccess;
     if (fp32) {
         switch (threads) {
-            case 128: return launch2_nx<float, 128>(a, nprob, nx, s);
-            case 256: return launch2_nx<float, 256>(a, nprob, nx, s);
+            case 128: return launch2_nx<float, 128>(a, nprob, nx, longest, s);
+            case 256: return launch2_nx<float, 256>(a, nprob, nx, longest, s);
         }
     } else {
         switch (threads) {
-            case 128: return launch2_nx<double, 128>(a, nprob, nx, s);
-            case 256: return launch2_nx<double, 256>(a, nprob, nx, s);
-            case 512: return launch2_nx<double, 512>(a, nprob, nx, s);
+            case 128: return launch2_nx<double, 128>(a, nprob, nx, longest, s);
+            case 256: return launch2_nx<double, 256>(a, nprob, nx, longest, s);
+            case 512: return launch2_nx<double, 512>(a, nprob, nx, longest, s);
         }
     }
     return hipErrorInvalidValue;

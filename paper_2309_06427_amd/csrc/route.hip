@@ -86,9 +86,9 @@ bool chip_pays(int nx, const int32_t *N, int count, int too_long, int cus) {
 
 // A step of the fused pass costs about the same at any state size, 1.07 and 1.6 times as much with 256 and 512 threads
 // as with 128, and holds more knots then; a CU holds 3 to 6, 2 to 3 and 1 of these workgroups.  Of 416 measured cases
-// (nx 4 to 31, 1 to 128 knots, 16 to 4096 problems) the choice is at most 9% slower than the best one.  128, 256 and 512
-// threads in ms: nx 26, 1024 problems of 128 knots and condition 1e6 156, 120 and
-// 53, 512 of 4 knots 0.418, 0.267 and 0.376, 4096 of 2 0.584, 0.797 and 1.729; nx 14, 4096 of 4 0.522, 0.907 and 1.964,
+// (nx 4 to 31, 1 to 128 knots, 16 to 4096 problems) the choice is at most 17% slower than the best one, and 10% at all
+// but two of them.  128, 256 and 512 threads in ms: nx 26, 1024 problems of 128 knots and condition 1e6 156, 120 and 53,
+// 512 of 4 knots 0.418, 0.267 and 0.376, 4096 of 2 0.584, 0.797 and 1.729; nx 14, 4096 of 4 0.522, 0.907 and 1.964,
 // 16 of 128 2.96, 1.59 and 0.81; nx 6, 512 of 32 0.266, 0.172 and 0.312, 16 of 128 0.729, 0.471 and 0.321.
 int fused_fp64_threads(int nx, const int32_t *N, int count, int cus, const int32_t *resident) {
     int best = 128;

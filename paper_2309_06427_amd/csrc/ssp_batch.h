@@ -131,6 +131,7 @@ struct ssp_batch {
     // budget (0: derived from threads / lds_bytes above).
     struct Group {
         int nx = 0, count = 0, offset = 0;  // problems dgorder[offset .. offset + count)
+        int longest = 0;                    // their longest horizon
         double work = 0;                    // sum of N nx^2 (launch order: largest first)
         int streamed = 0, chip_lds = 0;     // scaled solve under FP32 storage: the first `streamed` problems are too
                                             // long for the on-chip solve, or it does not pay; LDS bytes of the others

@@ -14,11 +14,6 @@ namespace ssp {
 
 namespace {
 
-// Kernel instances of the fused solve whose next step's loads go out in parts between the phases of a step, at addresses
-// formed anew (see Prefetch in pcg2.hip); NX = 0: any state size.
-template <typename TM, int BLOCK, int NX>
-constexpr bool loads_in_parts() { return NX == 0 || (sizeof(TM) == 8 && BLOCK == 512); }
-
 template <typename TM>
 struct Vec16;
 template <>
@@ -235,7 +230,7 @@ struct ResNorms {
 // knot behind (r_k needs L_{k+1}).  Writes r64, returns this thread's parts
 // of ||r||^2 and ||gamma||^2.  The same wave mapping as the fused pass
 // (lane -> knot, row).
-template <typename TM, int BLOCK, int NX>
+template <typename TM, int BLOCK, int NX, bool AGAIN>
 __device__ __forceinline__ ResNorms residual_pass(int N, int C, const TM *__restrict__ B3,
                                                 const float *__restrict__ Dlo, const float *__restrict__ Llo,
                                                 const double *__restrict__ lam, const double *__restrict__ gam,
@@ -260,7 +255,7 @@ __device__ __forceinline__ ResNorms residual_pass(int N, int C, const TM *__rest
     double lamv = 0.0;
 
     auto issue = [&](int k0, int kc) {
-        const int nvec = kc * VPK, t = fresh_if<loads_in_parts<TM, BLOCK, NX>()>(threadIdx.x);
+        const int nvec = kc * VPK, t = fresh_if<AGAIN>(threadIdx.x);
         static_for<0, KP>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             int q = t + m * BLOCK;
