@@ -110,6 +110,22 @@ int chip_count(const ssp_batch *b, const ssp_batch::Group &g) {
     return ssp::pcg3_steps_for(g.nx, b->fp32, t, lds, m) > m + 1 ? g.count - g.streamed : 0;
 }
 
+// Workgroup size of the FP64 fused solve for a group without a chosen mapping, found when it is first asked for (the
+// current device is the handle's), at the latest with the first FP64 storage: a solve, which may be captured, only reads it.
+int fp64_threads(const ssp_batch *b, const ssp_batch::Group &g) {
+    if (g.fp64_threads == 0) {
+        std::vector<int32_t> horizons;
+        for (int p = 0; p < b->P; ++p)
+            if (b->nx[p] == g.nx) horizons.push_back(b->N[p]);
+        std::sort(horizons.begin(), horizons.end(), std::greater<int32_t>());
+        int32_t resident[3];
+        for (int q = 0; q < 3; ++q)
+            resident[q] = ssp::pcg2_fp64_resident(g.nx, 128 << q, ssp::pcg2_lds(g.nx, false, 128 << q));
+        g.fp64_threads = ssp::fused_fp64_threads(g.nx, horizons.data(), g.count, b->cus, resident);
+    }
+    return g.fp64_threads;
+}
+
 ssp_status alloc_storage(ssp_batch *b, bool fp32) {
     if (b->have_storage && b->fp32 == fp32) return SSP_OK;
     free_storage(b);
@@ -136,25 +152,11 @@ ssp_status alloc_storage(ssp_batch *b, bool fp32) {
     }
     b->fp32 = fp32;
     b->have_storage = true;
+    if (!fp32)
+        for (const auto &g : b->groups) (void)fp64_threads(b, g);
     return SSP_OK;
 }
 
-
-// Workgroup size of the FP64 fused solve for a group without a chosen mapping, found when it is first asked for (the
-// current device is the handle's).
-int fp64_threads(const ssp_batch *b, const ssp_batch::Group &g) {
-    if (g.fp64_threads == 0) {
-        std::vector<int32_t> horizons;
-        for (int p = 0; p < b->P; ++p)
-            if (b->nx[p] == g.nx) horizons.push_back(b->N[p]);
-        std::sort(horizons.begin(), horizons.end(), std::greater<int32_t>());
-        int32_t resident[3];
-        for (int q = 0; q < 3; ++q)
-            resident[q] = ssp::pcg2_fp64_resident(g.nx, 128 << q, ssp::pcg2_lds(g.nx, false, 128 << q));
-        g.fp64_threads = ssp::fused_fp64_threads(g.nx, horizons.data(), g.count, b->cus, resident);
-    }
-    return g.fp64_threads;
-}
 
 // Workgroup size and LDS bytes of the fused kernel for one solve group, or
 // lds = 0 if its knots do not fit the fused kernel's registers or LDS.

@@ -27,6 +27,7 @@ for dev, sizes, prec, pc in eval(sys.stdin.read()):
     h = C.c_void_p()
     assert L.ssp_batch_create(len(N), p(N), p(nx), p(nx // 2), dev, C.byref(h)) == 0
     assert L.ssp_build(h, pc, prec, mem, mem, mem, mem, mem, stream) == 0
+    C.CDLL(None).fflush(None)
     print("solve", flush=True)
     assert L.ssp_solve(h, 1e-6, 0, mem, mem, 0, mem, mem, mem, stream) == 0
     C.CDLL(None).fflush(None)
@@ -110,3 +111,14 @@ def test_one_state_size_stays_on_the_callers_stream(fake):
         assert {w[0] for w in calls_} <= {"launch", "allow"}
         solves = [w for w in calls_ if w[0] == "launch" and int(w[3]) > 0]
         assert [int(w[6]) for w in solves] == blocks and {w[4] for w in solves} == {"0x5000"}
+
+
+def test_solves_ask_the_runtime_for_nothing_but_launches_after_the_first(fake):
+    """Once a process has run a solve of a kind, further ones, also of new handles, make launches, event records and waits
+    only, as a capture needs it."""
+    some = [(60, 14), (40, 26), (90, 6), (30, 36)]
+    work = [(0, sizes, p, SYM) for sizes in (some, some + [(20, 9)]) for p in (REFINE, FP64)]
+    _, solves = calls(fake, work * 2)
+    for first, again in zip(solves[:4], solves[4:]):
+        assert {w[0] for w in again} == {"launch", "record", "wait"} and len(again) >= 7
+        assert {w[0] for w in first} - {"allow"} == {"launch", "record", "wait"}
