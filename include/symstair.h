@@ -195,7 +195,7 @@ ssp_status ssp_solve(ssp_batch *b, double rel_tol, int32_t max_iter, const doubl
 /* ssp_solve for callers that cannot allocate device memory at call time
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, kernels and results, but the solve workspace
- * (the persistent grid's work counter, the FP64 residual vectors and the
+ * (the persistent grids' work counters, the FP64 residual vectors and the
  * seven inner-precision vectors, about 72 bytes per entry of lambda in FP64
  * storage, 44 in FP32 storage) lives in one fixed array of
  * SSP_NOALLOC_SCRATCH_BYTES per device, held from the library's first use
@@ -205,7 +205,7 @@ ssp_status ssp_solve(ssp_batch *b, double rel_tol, int32_t max_iter, const doubl
  * than the array holds; SSP_ERR_STATE as for ssp_solve, and when the
  * explicit-block kernel would first have to allocate its stair blocks (run
  * one ssp_solve or ssp_export with the handle before).  Every call on a
- * device shares that device's array (the work counter is reset by a fill
+ * device shares that device's array (the work counters are reset by a fill
  * kernel at each call; the vectors are written before they are read): calls
  * whose execution overlaps on one device, from any handle, thread or
  * stream, race and give undefined results. */
@@ -268,9 +268,11 @@ ssp_status ssp_export(ssp_batch *b, int which, double *diag, double *off, void *
  *   3 = the cooperative solve for a batch of one problem of any length whose
  *       grid fits (else as 0): the same method with the problem's knots
  *       spread over the grid, four per workgroup, and grid-wide barriers;
- *   4 = the scaled solve: one persistent grid for the whole batch, problems
- *       taken largest first from a device queue, each PCG pass streaming the
- *       Oh_k blocks of the congruence basis (see ssp_build).  With kernel 0
+ *   4 = the scaled solve in the congruence basis (see ssp_build): persistent
+ *       grids per state size, problems taken largest first from device queues,
+ *       each PCG pass applying the Oh_k blocks.  A problem either streams them
+ *       or, under FP32 storage, is held on one CU for the whole inner solve
+ *       (see ssp_scaled_onchip_problems).  With kernel 0
  *       the build chooses it for the polynomial preconditioners and for
  *       block-Jacobi and both stairs under FP32 storage (except a single
  *       problem of N >= 24 knots, which runs the cooperative solve).
@@ -348,8 +350,8 @@ ssp_status ssp_gemm_f32(int32_t M, int32_t N, int32_t K, const float *A, int32_t
  * own workgroup size and LDS budget (the budget sets the knots per pipeline
  * step, hence workgroups per CU).  ssp_autotune times every candidate
  * mapping (128, 256 or, under FP64 storage, 512 threads; the largest step and
- * two shorter ones) on each group alone with this batch's last build and keeps the fastest; it
- * then solves the whole batch once, so the outputs (same meaning as in
+ * two shorter ones) on each group alone with this batch's last build and keeps
+ * the fastest; it then solves the whole batch once, so the outputs (same meaning as in
  * ssp_solve, zero start, max_iter = 10 N nx) hold valid results.  It
  * synchronises the stream and must not be captured into a graph.
  * ssp_set_mapping clears the tuned choice.  With nothing to tune (the
@@ -394,40 +396,39 @@ ssp_status ssp_set_reduction_fp64(ssp_batch *b, int32_t on);
  * no pipeline step from the budget. */
 ssp_status ssp_set_scaled_mapping(ssp_batch *b, int32_t threads, int32_t lds_bytes);
 /* The scaled solve's mapping: threads, LDS bytes, workgroups of each
- * persistent grid on this device (min(resident workgroups, nprob); one grid
- * runs per state size of the batch) and the autotuner's best time in ms (0 if
- * not tuned); any pointer may be NULL. */
+ * streaming grid on this device (min(resident workgroups, nprob); one runs per
+ * state size with streaming problems) and the autotuner's best time in ms (0
+ * if not tuned); any pointer may be NULL.  The on-chip form, which the default
+ * mapping allows, has workgroups of its own, one per CU. */
 ssp_status ssp_get_scaled_mapping(const ssp_batch *b, int32_t *threads, int32_t *lds_bytes, int32_t *grid,
                                   float *tuned_ms);
-/* The largest horizon N whose six PCG recurrence vectors the scaled solve
- * keeps in the workgroup's LDS instead of HBM, for state size nx,
- * preconditioner pc, storage precision prec and a mapping of threads (128
- * or 256) and lds_bytes (as ssp_get_scaled_mapping reports it): problems
- * with N <= *max_n stream only the Oh blocks per pass.  0 = none (state
- * sizes above 14 never).  A pure function of its arguments (no device call);
- * SSP_ERR_ARG for a NULL max_n or an unknown pc or prec. */
+/* The largest horizon N whose six PCG recurrence vectors the streaming form of
+ * the scaled solve keeps in the workgroup's LDS instead of HBM, for state size
+ * nx, preconditioner pc, storage precision prec and a mapping of threads (128
+ * or 256) and lds_bytes (as ssp_get_scaled_mapping reports it): streaming
+ * problems with N <= *max_n stream only the Oh blocks per pass.  0 = none
+ * (state sizes above 14 never stream so).  A pure function of its arguments
+ * (no device call); SSP_ERR_ARG for a NULL max_n or an unknown pc or prec. */
 ssp_status ssp_scaled_onchip_horizon(int32_t nx, ssp_precon pc, ssp_precision prec, int32_t threads,
                                      int32_t lds_bytes, int32_t *max_n);
 
 /* How many problems of state size nx the next ssp_solve of the current build
  * holds on chip: in the scaled solve under FP32 storage, with the default
  * mapping and FP32 sums (ssp_set_reduction_fp64 off), a problem of state size
- * 6, 14 or 26 whose vectors fit a CU's LDS can run with its Oh blocks in
- * registers and L2 and its vectors in LDS instead of streaming them each pass.
- * They are the shortest *count problems of that state size; the others
- * stream.  Both forms return the same bits.  0 where streaming all of them is
- * expected to be faster (many short horizons, a few too long ones) and under
- * any other solve; SSP_ERR_ARG for a null count or a state size that the batch does not have,
+ * 6, 14 or 26 whose vectors fit a CU's LDS can run with its vectors there and
+ * Oh blocks in registers instead of streaming them each pass.  They are the
+ * shortest *count problems of that state size; the others stream.  Both forms
+ * return the same bits.  0 where streaming all of them is expected to be
+ * faster (many short horizons, a few too long ones) and under any other solve;
+ * SSP_ERR_ARG for a null count or a state size that the batch does not have,
  * SSP_ERR_STATE before the first build. */
 ssp_status ssp_scaled_onchip_problems(const ssp_batch *b, int32_t nx, int32_t *count);
 
 /* The kernel the last ssp_solve (or ssp_autotune) of this batch enqueued:
  * 1 explicit two-sweep, 2 fused (one workgroup per problem), 3 cooperative
- * (one problem over the whole grid), 4 scaled (a persistent grid per state
- * size); 0 before
- * any solve.  *W and *G (may be
- * NULL) receive the cooperative plan: own knots per workgroup and
- * workgroups (0 for the other kernels). */
+ * (one problem over the whole grid), 4 scaled (persistent grids per state
+ * size); 0 before any solve.  *W and *G (may be NULL) receive the cooperative
+ * plan: own knots per workgroup and workgroups (0 for the other kernels). */
 ssp_status ssp_solve_kernel(const ssp_batch *b, int32_t *kernel, int32_t *W, int32_t *G);
 
 /* Human-readable text of a call-level status, and of the last HIP error seen

@@ -4,9 +4,11 @@
 // (forward, residual loss, backward, Adam) run in these kernels.
 //
 // Every product is an FP32 GEMM on the matrix cores
-// (v_mfma_f32_16x16x4_f32): 32 x 32 output tiles per 256-thread workgroup,
-// each wave one MFMA tile, K staged through two LDS buffers 32 at a time.  Operand loaders read the network inputs straight from the stored
-// blocks (no feature matrix is materialised) and the epilogues fuse bias,
+// (v_mfma_f32_16x16x4_f32): 32 x 32 output tiles per 256-thread workgroup
+// (32 x 64 for the first layer's weight gradient from 256 inputs on), each wave
+// one MFMA tile (two), K staged through two LDS buffers 32 at a time.  Operand
+// loaders read the network inputs straight from the stored blocks (no feature
+// matrix is materialised) and the epilogues fuse bias,
 // GELU and its derivative.  Weight gradients reduce over the knots with a
 // fixed K split and a fixed-order sum, so training steps are reproducible.
 #include <math.h>

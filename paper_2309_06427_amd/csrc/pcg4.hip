@@ -5,8 +5,9 @@
 // and vectors through HBM.  One workgroup of eight waves owns a CU and a problem; the knots are dealt out in sets of
 // four, each wave holds a contiguous range of sets, and the first RS sets of every wave stay in its registers for
 // the whole inner solve.  The sets beyond those are read again at each product, forwards for the Horner products and
-// backwards for w, so that the last ones read are the first ones needed and come from L2.  The vectors r, u and w
-// (and p, s and x where they fit) live in LDS.
+// backwards for w, so that the last ones read are the first ones needed.  (At nx 26 one in four of these reads hits L2:
+// a CU's share of it is 128 KB, the blocks of 144 knots are 390 KB.  The others, 19 GB of the ragged 4096-problem batch's
+// solve, come from past it.)  The vectors r, u and w (and p, s and x where they fit) live in LDS.
 //
 // A set puts knot 4 s + g on lanes 16 g .. 16 g + P - 1 of a wave; lane p holds rows p and (R = 2) p + P of Oh_k.
 // The product with v needs, per block, a_k = Oh_k v_{k-1} (row i in one lane: every term is one multiply-add whose

@@ -46,7 +46,7 @@ hipError_t dalloc(T **p, size_t count) {
 // Solve workspace of one call: the handle's own, or the library's fixed
 // device array (the allocation-free entry point).
 struct SolveScratch {
-    unsigned *queue = nullptr;  // persistent grid's work counter (1 word)
+    unsigned *queue = nullptr;  // work counters of the persistent grids (two words per group: streaming, on chip)
     double *r64 = nullptr;      // FP64 residual, tot_v long
     double *rh64 = nullptr;     // FP64 residual in the scaled basis, tot_v long
     void *work = nullptr;       // 7 vectors of the storage precision, tot_v long each
@@ -99,7 +99,7 @@ struct ssp_batch {
     int32_t *douter = nullptr;
     // scaled basis (built when the scaled solve will run): Z_k, Oh_k in the
     // storage type (full blocks, stride bs), Z_k in FP64 (build only), the
-    // scaled residual and the persistent grid's queue counter
+    // scaled residual and the persistent grids' queue counters
     void *Zs = nullptr, *OH = nullptr;
     double *rh64 = nullptr;
     unsigned *dqueue = nullptr;
