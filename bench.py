@@ -23,29 +23,30 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM bytes per launch of the solve kernel from rocprofv3 FETCH_SIZE and
+# Bytes past L2 (HBM and the Infinity Cache) per launch of the solve kernels from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE (KiB per dispatch), each scaled by what the counter reads for a
 # plain copy of known size (2.0 and 1.0), keyed by the workload/settings and by
 # a hash of the kernel's sources: a changed kernel reports null.
 # the scaled solve's device code and the host code that sets its launch and stopping parameters
-SOLVE_SOURCES = ("pcg3.hip", "pcg4.hip", "ssp_scaled.h", "ssp_fused.h", "ssp_device.h", "ssp_host.h", "host.hip")
+SOLVE_SOURCES = ("pcg3.hip", "pcg4.hip", "ssp_scaled.h", "ssp_sweep.h", "ssp_fused.h", "ssp_device.h", "ssp_host.h",
+                 "route.hip", "host.hip")
 MEASURED_TRAFFIC = {
-    # (workload, pc, precision, kernel): (sources sha256[:16], HBM bytes of one solve): rocprofv3 FETCH_SIZE x 2.0
-    # + WRITE_SIZE x 1.0 (KiB, the factors a plain 1 GiB copy reads), summed over the three k_pcg3 instances (nx 6,
-    # 14, 26) of one solve at 256 threads / 48 336 B
+    # (workload, pc, precision, kernel): (sources sha256[:16], bytes of one solve): rocprofv3 FETCH_SIZE x 2.0
+    # + WRITE_SIZE x 1.0 (KiB, the factors a plain 1 GiB copy reads), summed over k_pcg4<26>, k_pcg4<14> and the
+    # k_pcg3 instance of nx 6 in one solve at the default mapping
     ("batch4096_ragged", "sym", "fp32_refine64", 0):
-        ("7832a2dd28d9765a", ((8431864.3125 + 2908337.1875 + 148507.75) * 2.0
-                              + (2916113.21875 + 1499994.59375 + 41748.65625) * 1.0) * 1024),
+        ("a05c4c5c97a7e782", ((9277937.09375 + 618255.4375 + 475463.59375) * 2.0
+                              + (940396.703125 + 231562.234375 + 516222.953125) * 1.0) * 1024),
 }
 
-# The KKT step's HBM bytes per call, the same counters and factors, summed
+# The KKT step's bytes per call, the same counters and factors, summed
 # over the kernels of the three state sizes (nx 26, 14, 6): (sources
 # sha256[:16], right-hand side bytes, recovery bytes)
 KKT_SOURCES = ("kkt.hip", "ssp_host.h", "host.hip")
 MEASURED_KKT_TRAFFIC = {
-    "batch4096_ragged": ("f647674a887fd787",
-                         ((1431882.47 + 443152.46 + 90428.95) * 2.0 + (38557.83 + 21607.56 + 9358.26) * 1.0) * 1024,
-                         ((1521470.02 + 464100.26 + 92836.45) * 2.0 + (65205.94 + 34264.34 + 14283.5) * 1.0) * 1024),
+    "batch4096_ragged": ("3a42cb91ef0f6ce0",
+                         ((1431872.22 + 444173.56 + 90416.5) * 2.0 + (39172.83 + 22193.0 + 9356.92) * 1.0) * 1024,
+                         ((1521379.19 + 464055.88 + 92820.19) * 2.0 + (65205.94 + 34264.34 + 14283.69) * 1.0) * 1024),
 }
 
 
@@ -444,7 +445,8 @@ def main() -> int:
         split = {"block_bytes": float(bb.sum()), "vector_bytes": float(vb.sum()),
                  "problems_with_vectors_in_lds": int((oc | ch).sum()), "problems_on_chip": int(ch.sum())}
     rec = MEASURED_TRAFFIC.get((args.workload, args.pc, precision, args.kernel))
-    traffic = rec[1] if rec and rec[0] == solve_sources_hash() else None
+    # (the record is of the default mapping, the one that has problems on chip)
+    traffic = rec[1] if rec and rec[0] == solve_sources_hash() and kern == 4 and ch.any() else None
     solve_avg_s = float(plain["solve_ms"].mean()) / 1e3
     achieved = bytes_solve / solve_avg_s / 1e9
     value = b.P * args.steps / head_wall
@@ -585,17 +587,20 @@ def main() -> int:
         },
         "roofline": {
             "kernel": {1: "k_pcg", 2: "k_pcg2", 3: "k_coop", 4: "k_pcg4 and k_pcg3" if kern == 4 and ch.any() else "k_pcg3"}[kern],
-            "bound": "hbm",
+            "bound": ("latency" if kern == 3 else
+                      "issue and lds (on chip), hbm (streaming)" if kern == 4 and ch.any() else "hbm"),
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
+            "traffic_frac": round(traffic / solve_avg_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
             **({"note": "latency-bound: blocks stay in LDS, one grid-wide sum per PCG iteration"}
                if kern == 3 else
                {"note": "one persistent instance per state size, run concurrently; achieved and traffic cover "
-                        "all of them over the solve phase; problems held on chip count their blocks once per inner "
-                        "solve, their passes are bound by LDS and latency"} if kern == 4 else {}),
+                        "all of them over the solve phase; achieved counts the blocks of a problem held on chip once "
+                        "per inner solve, traffic what passes L2 (sets of blocks beyond the registers again at each "
+                        "product, served by HBM and the Infinity Cache)"} if kern == 4 else {}),
         },
         "cpu_baseline": cpu,
     }
